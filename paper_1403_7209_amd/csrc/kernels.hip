@@ -1068,6 +1068,193 @@ __global__ __launch_bounds__(NT, (OwnerTune<T, Op>::WAVES > 0 ? OwnerTune<T, Op>
     }
 }
 
+// ------------------------------------------- fixed-order owner kernel -- */
+
+// What a visit hands over through LDS: NM values per edge, from which term(v)
+// forms the increment v.
+template <class Op>
+struct Message {
+    using type = Op;
+    static constexpr int NM = Op::NOUT;
+    template <int NT>
+    __device__ static __forceinline__ double term(const double *Y, int v, int slot)
+    {
+        return Y[v * NT + slot];
+    }
+};
+
+// The Green-Gauss sums: the 18 products f_v n_d from their 9 factors.
+struct OpGradM : OpGrad {
+    template <typename T>
+    __device__ static __forceinline__ void edge(const T *a, const T *b, const T *n, T,
+                                                double *y, double *, double *)
+    {
+#pragma unroll
+        for (int v = 0; v < 6; ++v) y[v] = (double)(T(0.5) * (a[v] + b[v]));
+#pragma unroll
+        for (int d = 0; d < 3; ++d) y[6 + d] = (double)n[d];
+    }
+};
+template <>
+struct Message<OpGrad> {
+    using type = OpGradM;
+    static constexpr int NM = 9;
+    template <int NT>
+    __device__ static __forceinline__ double term(const double *Y, int v, int slot)
+    {
+        return Y[(v / 3) * NT + slot] * Y[(6 + v % 3) * NT + slot];
+    }
+};
+
+// WAVES: waves per SIMD the registers must allow (three workgroups per CU where
+// the LDS holds three: the FP64 flux stage of a 1M-node RCM mesh takes 190 us
+// with 24 wavefronts per CU, 225 us with 16).  AHEAD: entries of a node's list
+// fetched before the round's flux is computed.
+template <typename T, class Op>
+struct FixedTune {
+    static constexpr int WAVES = 6, AHEAD = 4;
+};
+template <>
+struct FixedTune<double, OpAdjoint> {
+    static constexpr int WAVES = 4, AHEAD = 1;
+};
+template <>
+struct FixedTune<double, OpGrad> {
+    static constexpr int WAVES = 4, AHEAD = 4;
+};
+template <>
+struct FixedTune<double, OpFlux2> {
+    static constexpr int WAVES = 1, AHEAD = 4;
+};
+
+struct FixedPtrs {
+    const int *rnd_off, *ent_base;
+    const uint32_t *off;
+    const uint16_t *ent;
+};
+
+// The owner loop with every sum in a fixed order (no LDS atomics): the chunk's
+// visits (interior block, then cut visits) go in rounds of NT, one per thread;
+// each puts its values into an LDS slot, and after a barrier every node adds
+// the slots of its own edges in list order into registers.  The result is the
+// same bit for bit on every run.  KC > 0 fixes the chunk size; with KC < NT the
+// NT / KC threads of a node share its NOUT sums.
+// It serves the coloured variant: against one launch per partition colour, each
+// re-reading and re-writing the nodes' totals with a barrier per edge colour,
+// one launch that writes each total once (FP64 flux of a 1M-node mesh in RCM
+// order: 740 -> 190 us).  What bounds it there is latency: 64 % of the edges are
+// cut, a chunk takes 11 rounds of two dependent trips to memory and two
+// barriers, and its wavefronts wait 80 % of their time (LDS pipe 30 % busy).
+// The owner kernel's atomics need no rounds and take 110 us on that mesh, but
+// their order varies.
+template <typename T, class Op, int KC>
+__global__ __launch_bounds__(kOwnerThreads, (FixedTune<T, Op>::WAVES)) void k_edge_fixed(
+    OwnerPtrs p, FixedPtrs f, Arrays<T> a, T gamma, int N, int Kr, int ncl, int remap)
+{
+    constexpr int NT = kOwnerThreads;
+    using M = Message<Op>;
+    constexpr int P = NT / (KC > 0 ? KC : NT);       // threads per node
+    constexpr int NV = (Op::NOUT + P - 1) / P;       // sums per thread
+    constexpr int NPH = Op::MODE == GEN ? 2 : 1;     // one hand-over per end where they differ
+    const int K = KC > 0 ? KC : Kr;
+    extern __shared__ __align__(16) unsigned char smem[];
+    T *ss = reinterpret_cast<T *>(smem);
+    double *Y = reinterpret_cast<double *>(smem + stage_bytes<T, Op>(K));
+    const int t = (int)threadIdx.x;
+    const int c = remap ? xcd_map((int)blockIdx.x, ncl) : (int)blockIdx.x;
+    const int v0 = c * K, nown = min(K, N - v0);
+    const int2 ib = p.iblk[c];
+    const int s0 = p.cv_off[c], n = ib.y + p.cv_off[c + 1] - s0;
+    const int r0 = f.rnd_off[c];
+    for (int v = t; v < nown; v += NT) {
+        T rec[Op::NS];
+        load_stage<Op>(a, v0 + v, gamma, rec);
+        lds_put<T, Op::NS>(ss, K, v, rec);
+    }
+    const int node = P > 1 ? t % K : t, vb = P > 1 ? (t / K) * NV : 0;
+    const bool sums = node < nown && vb < Op::NOUT;
+    double acc[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) acc[i] = 0.0;
+    __syncthreads();
+
+    auto range = [&](int r) { return sums ? f.off[(size_t)r * K + node] : 0u; };
+    uint32_t rg = n > 0 ? range(r0) : 0u;
+    for (int r = r0, b = 0; b < n; ++r, b += NT) {
+        // this round's entries of the thread's node, the first few fetched early
+        constexpr int AHEAD = FixedTune<T, Op>::AHEAD;
+        const uint16_t *en = f.ent + f.ent_base[r];
+        const int j0 = (int)(rg & 0xffffu), j1 = (int)(rg >> 16);
+        uint32_t pre[AHEAD];
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) pre[i] = j0 + i < j1 ? en[j0 + i] : 0u;
+
+        const int k = b + t;
+        double m[M::NM], m2[M::NM], wo[3] = {0.0, 0.0, 0.0};
+        T w[Op::NW], sa[Op::NS], sb[Op::NS];
+        if (k < ib.y) {
+            const uint32_t wd = ld(p.iw, ib.x + k);
+#pragma unroll
+            for (int d = 0; d < Op::NW; ++d) w[d] = ld(a.w[d], ib.x + k);
+            lds_get<T, Op::NS>(ss, K, (int)(wd & 0x1fffu), sa);
+            lds_get<T, Op::NS>(ss, K, (int)((wd >> 16) & 0x1fffu), sb);
+            M::type::edge(sa, sb, w, gamma, m, m2, wo);
+            if constexpr (Op::NWOUT > 0) {
+#pragma unroll
+                for (int d = 0; d < 3; ++d) st(a.wo[d], ib.x + k, wo[d]);
+            }
+        } else if (k < n) {
+            const int s = s0 + k - ib.y;
+            const int eid = ld(p.cv_eid, s), oth = ld(p.cv_oth, s), own = (int)ld(p.cv_own, s);
+            const uint32_t second = (uint32_t)oth >> 31;
+#pragma unroll
+            for (int d = 0; d < Op::NW; ++d) w[d] = flip(ld(a.w[d], eid), second);
+            load_stage<Op>(a, oth & 0x7fffffff, gamma, sb);
+            lds_get<T, Op::NS>(ss, K, own, sa);
+            M::type::edge(sa, sb, w, gamma, m, m2, wo);
+            if constexpr (Op::NWOUT > 0) {
+                if (v0 + own < (oth & 0x7fffffff)) {  // written once, from the smaller end
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) st(a.wo[d], eid, flip(wo[d], second));
+                }
+            }
+        }
+        if (b + NT < n) rg = range(r + 1);
+#pragma unroll
+        for (int ph = 0; ph < NPH; ++ph) {
+            if (ph == 1 && b >= ib.y) break;  // cut visits hand over one end only
+            if (k < n) {
+#pragma unroll
+                for (int i = 0; i < M::NM; ++i) Y[i * NT + t] = ph ? m2[i] : m[i];
+            }
+            __syncthreads();
+            auto add = [&](uint32_t e) {
+                const int slot = (int)(e & 0x7fffu);
+                const uint32_t end = e >> 15;
+                if (NPH == 2 && (int)end != ph) return;
+#pragma unroll
+                for (int i = 0; i < NV; ++i) {
+                    if (P > 1 && vb + i >= Op::NOUT) break;
+                    const double y = M::template term<NT>(Y, vb + i, slot);
+                    acc[i] += Op::MODE == ANTI ? flip(y, end) : y;
+                }
+            };
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i)
+                if (j0 + i < j1) add(pre[i]);
+            for (int j = j0 + AHEAD; j < j1; ++j) add(en[j]);
+            __syncthreads();
+        }
+    }
+    if (!sums) return;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        if (P > 1 && vb + i >= Op::NOUT) break;
+        double *y = a.y[vb + i];
+        st(y, v0 + node, ld(y, v0 + node) + acc[i]);
+    }
+}
+
 // ------------------------------------------------------ reductions -- */
 
 template <typename T>
@@ -1396,12 +1583,47 @@ int run_owner_stage(const DevPlan &P, const EdgeArrays &a, const NodeArrays &na,
     return (int)hipGetLastError();
 }
 
+// Chunk sizes fixed at compile time: the default cluster size and the small
+// meshes'.
+template <typename T, class Op, class F>
+void fixed_kernels(F &&f)
+{
+    f(512, k_edge_fixed<T, Op, 512>);
+    f(kFixedFine, k_edge_fixed<T, Op, kFixedFine>);
+    f(0, k_edge_fixed<T, Op, 0>);
+}
+
+template <typename T, class Op>
+size_t fixed_lds(int K)
+{
+    return stage_bytes<T, Op>(K) + (size_t)Message<Op>::NM * kOwnerThreads * sizeof(double);
+}
+
+template <typename T, class Op>
+int run_fixed(const DevPlan &P, const EdgeArrays &a, double gamma, hipStream_t st, const LaunchOpts &lo)
+{
+    const FixedPlan &X = P.fixed;
+    const OwnerPtrs op{X.iblk, X.iw, X.cv_off, X.cv_eid, X.cv_oth, X.cv_own};
+    const FixedPtrs fp{X.rnd_off, X.ent_base, X.off, X.ent};
+    const size_t lds = fixed_lds<T, Op>(X.K);
+    bool done = false;
+    fixed_kernels<T, Op>([&](int K, auto *kern) {
+        if (done || (K != 0 && K != X.K)) return;
+        hipLaunchKernelGGL(kern, dim3(X.nchunk), dim3(kOwnerThreads), lds, st, op, fp,
+                           typed<T>(a), (T)gamma, P.N, X.K, X.nchunk, lo.xcd_remap);
+        done = true;
+    });
+    return (int)hipGetLastError();
+}
+
 template <typename T, class Op>
 int run_edge(int variant, const DevPlan &P, const EdgeArrays &a, double gamma, hipStream_t st,
              const LaunchOpts &lo)
 {
     switch (variant) {
-    case V_COLOURED: return run_coloured_bs<T, Op, false>(P, a, gamma, st, lo);
+    case V_COLOURED:
+        if (lo.fixed) return run_fixed<T, Op>(P, a, gamma, st, lo);
+        return run_coloured_bs<T, Op, false>(P, a, gamma, st, lo);
     case V_COLOURED_LDS_ATOMIC: return run_coloured_bs<T, Op, true>(P, a, gamma, st, lo);
     case V_ATOMIC: return run_atomic<T, Op>(P, a, gamma, st, lo);
     case V_OWNER: return run_owner<T, Op>(P, a, gamma, st, lo);
@@ -1462,6 +1684,9 @@ int raise_all(size_t bytes)
 {
     int rc = raise_coloured<T, Op, false>(bytes);
     if (!rc) rc = raise_coloured<T, Op, true>(bytes);
+    fixed_kernels<T, Op>([&](int, auto *kern) {
+        if (!rc) rc = raise_one(reinterpret_cast<const void *>(kern), bytes);
+    });
     using O = typename OwnerOp<Op>::type;
     constexpr bool H = OwnerOp<Op>::HALVES;
     constexpr int NT = OwnerTune<T, O>::NT;
@@ -1501,6 +1726,15 @@ size_t edge_lds_bytes(int op, bool fp32, int variant, int umax, int K)
     if (op == OP_SPECRAD)
         return fp32 ? lds_bytes<float, OpSpecrad>(rows) : lds_bytes<double, OpSpecrad>(rows);
     return fp32 ? lds_bytes<float, OpFlux>(rows) : lds_bytes<double, OpFlux>(rows);
+}
+
+size_t fixed_lds_bytes(int op, bool fp32, int K)
+{
+    if (op == OP_ADJOINT) return fixed_lds<double, OpAdjoint>(K);
+    if (op == OP_GRAD) return fixed_lds<double, OpGrad>(K);
+    if (op == OP_FLUX2) return fixed_lds<double, OpFlux2>(K);
+    if (op == OP_SPECRAD) return fp32 ? fixed_lds<float, OpSpecrad>(K) : fixed_lds<double, OpSpecrad>(K);
+    return fp32 ? fixed_lds<float, OpFlux>(K) : fixed_lds<double, OpFlux>(K);
 }
 
 int set_lds_limit(size_t bytes)

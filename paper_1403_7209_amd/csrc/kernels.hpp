@@ -20,6 +20,28 @@ enum Variant { V_COLOURED = 0, V_ATOMIC = 1, V_OWNER = 2, V_COLOURED_LDS_ATOMIC 
 
 constexpr int kOwnerThreads = 512;
 
+// Lists of the fixed-order owner loop (k_edge_fixed): chunk c owns the internal
+// nodes [c K, (c+1) K) and runs its interior block, then its cut visits, in
+// rounds of kOwnerThreads visits (rounds rnd_off[c] .. rnd_off[c+1]).  In round
+// r node k of the chunk adds up the entries ent[ent_base[r] + off[r (K+1) + k]
+// .. ent_base[r] + off[r (K+1) + k + 1]): the visit's slot in the round, bit 15
+// set when the node is the second end of an interior edge.
+struct FixedPlan {
+    int K = 0, nchunk = 0;  // K = 0: no lists
+    const int2 *iblk = nullptr;
+    const uint32_t *iw = nullptr;
+    const int *cv_off = nullptr, *cv_eid = nullptr, *cv_oth = nullptr;
+    const uint16_t *cv_own = nullptr;
+    const int *rnd_off = nullptr, *ent_base = nullptr;
+    const uint32_t *off = nullptr;
+    const uint16_t *ent = nullptr;
+};
+// The largest chunk of the fixed-order loop: one node per thread.
+constexpr int kFixedMaxK = kOwnerThreads;
+// The chunk of a small mesh, and the most nodes of one (see fixed_chunk).
+constexpr int kFixedFine = 32;
+constexpr int kFixedFineNodes = 65536;
+
 // Device copy of an execution plan (internal numbering, int32 offsets).
 struct DevPlan {
     int N = 0, E = 0, nb = 0, nc = 0, umax = 0, block_size = 0;
@@ -50,6 +72,7 @@ struct DevPlan {
     // the same visits ordered by foreign node within each run (same offsets)
     const int *cvf_eid = nullptr, *cvf_oth = nullptr;
     const uint16_t *cvf_own = nullptr;
+    FixedPlan fixed;
     // flat colouring: colour c runs edges flat_eid[flat_off[c] .. flat_off[c+1])
     double *stage_partial = nullptr;  // kSumTail + [ncl][6]: partial sums of the fused stage
     int nflat = 0;
@@ -69,6 +92,7 @@ struct EdgeArrays {
 struct LaunchOpts {
     int xcd_remap = 1;  // give each XCD a contiguous range of partitions/clusters
     int overwrite = 0;  // owner variant: res = sum instead of res += sum
+    int fixed = 0;      // coloured variant: through the plan's fixed-order lists
 };
 
 // Returns 0 or a hipError_t value.
@@ -203,6 +227,9 @@ int launch_local_dt(int N, const double *vol, const double *lam, double cfl, dou
 
 // LDS bytes (dynamic and static) of one workgroup of an edge loop.
 size_t edge_lds_bytes(int op, bool fp32, int variant, int umax, int K);
+
+// LDS bytes of one workgroup of the fixed-order loop over chunks of K nodes.
+size_t fixed_lds_bytes(int op, bool fp32, int K);
 
 // Lets every edge kernel instance use up to `bytes` of LDS in total.
 int set_lds_limit(size_t bytes);

@@ -218,6 +218,54 @@ int upload_owner(opf_ctx *ctx, PlanRec &pr)
     return rc;
 }
 
+// Nodes per chunk of the fixed-order loop: the owner clusters' size, or 32 up to
+// 65,536 nodes.  There 512-node chunks number at most 128, a workgroup each on
+// 256 CUs, and a chunk's 11 rounds follow one another; 32-node chunks run every
+// edge from both ends but take one round each.  Five stages of the FP64 flux
+// with 512- and 32-node chunks: 8,000 nodes 227 and 111 us, 46,656 nodes 247 and
+// 181 us; 216,000 nodes 370 and 648 us (all with a separate stage update).
+int fixed_chunk(const opf::Plan &P)
+{
+    const int K = P.cluster_size;
+    if (K <= 0 || K > opf::gpu::kFixedMaxK) return 0;
+    const bool fine = P.N > K && K > opf::gpu::kFixedFine && P.N <= opf::gpu::kFixedFineNodes;
+    return fine ? opf::gpu::kFixedFine : K;
+}
+
+// The fixed-order loop's arrays (see FixedPlan).
+int upload_fixed(opf_ctx *ctx, PlanRec &pr)
+{
+    opf::gpu::DevPlan &D = pr.dev;
+    opf::gpu::FixedPlan &X = D.fixed;
+    const int K = fixed_chunk(pr.host);
+    if (!K) return OPF_OK;
+    opf::FixedLists F;
+    opf::build_fixed(pr.host, K, opf::gpu::kOwnerThreads, F);
+    int rc = OPF_OK;
+    if (F.fine) {
+        std::vector<int2> iblk(F.iblk.size() / 2, make_int2(0, 0));
+        rc = upload(ctx, pr, iblk, X.iblk);
+        if (!rc) rc = upload(ctx, pr, F.cv_off, X.cv_off);
+        if (!rc) rc = upload(ctx, pr, F.cv_eid, X.cv_eid);
+        if (!rc) rc = upload(ctx, pr, F.cv_oth, X.cv_oth);
+        if (!rc) rc = upload(ctx, pr, F.cv_own, X.cv_own);
+    } else {
+        X.iblk = D.iblk;
+        X.cv_off = D.cv_off;
+        X.cv_eid = D.cvf_eid;
+        X.cv_oth = D.cvf_oth;
+        X.cv_own = D.cvf_own;
+    }
+    X.iw = D.iw;
+    if (!rc) rc = upload(ctx, pr, F.rnd_off, X.rnd_off);
+    if (!rc) rc = upload(ctx, pr, F.ent_base, X.ent_base);
+    if (!rc) rc = upload(ctx, pr, F.off, X.off);
+    if (!rc) rc = upload(ctx, pr, F.ent, X.ent);
+    X.K = K;
+    X.nchunk = (int)(F.rnd_off.size() - 1);
+    return rc;
+}
+
 int upload_plan(opf_ctx *ctx, PlanRec &pr)
 {
     const opf::Plan &P = pr.host;
@@ -252,6 +300,7 @@ int upload_plan(opf_ctx *ctx, PlanRec &pr)
     if (D.owner_ok) {
         if (P.cluster_size > 8192) return ctx->fail(OPF_EINVAL, "cluster_size above 8192");
         rc = upload_owner(ctx, pr);
+        if (!rc && P.coloured_ok) rc = upload_fixed(ctx, pr);
         if (!rc) {
             const size_t nb = sizeof(double) * (opf::gpu::kSumTail + 6 * (size_t)D.ncl);
             D.stage_partial = static_cast<double *>(ctx->dalloc(nb));
@@ -579,11 +628,17 @@ int edge_loop(opf_ctx *ctx, int kernel, opf_set s, int nargs, const opf_arg *arg
     if ((variant == OPF_V_COLOURED || variant == OPF_V_COLOURED_LDS_ATOMIC) && !pr.host.coloured_ok)
         return ctx->fail(OPF_EINVAL, "the plan has no two-level colouring (" + pr.host.coloured_why +
                                          "): use the OWNER or ATOMIC variant");
+    opf::gpu::LaunchOpts lo;
     if (variant != OPF_V_ATOMIC && variant != OPF_V_FLAT) {
-        const size_t lds = opf::gpu::edge_lds_bytes(op, fp32, variant, pr.dev.umax, pr.dev.K);
+        size_t lds = opf::gpu::edge_lds_bytes(op, fp32, variant, pr.dev.umax, pr.dev.K);
         if (lds > ctx->max_lds)
             return ctx->fail(OPF_EINVAL, "a workgroup needs " + std::to_string(lds) +
                                              " B of LDS; use a smaller block or cluster size");
+        if (variant == OPF_V_COLOURED && pr.dev.fixed.K > 0) {
+            const size_t fl = opf::gpu::fixed_lds_bytes(op, fp32, pr.dev.fixed.K);
+            lo.fixed = fl <= ctx->max_lds ? 1 : 0;
+            if (lo.fixed) lds = fl;
+        }
         if (lds > ctx->lds_limit) {
             int e = opf::gpu::set_lds_limit(ctx->max_lds);
             if (e) return hip_fail(ctx, (hipError_t)e, "raising the LDS limit");
@@ -613,7 +668,6 @@ int edge_loop(opf_ctx *ctx, int kernel, opf_set s, int nargs, const opf_arg *arg
         for (int c = 0; c < 3; ++c) ea.w[c] = comp(n, c);
     }
     const double gamma = want_gbl ? *static_cast<const double *>(gbls[0].ptr) : 0.0;
-    opf::gpu::LaunchOpts lo;
     lo.overwrite = overwrite ? 1 : 0;
     int e = opf::gpu::launch_edge(op, fp32, variant, pr.dev, ea, gamma, st, lo);
     if (e) return hip_fail(ctx, (hipError_t)e, "edge loop launch");

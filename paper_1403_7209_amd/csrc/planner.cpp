@@ -907,6 +907,85 @@ int build_plan(int64_t N, int64_t E, const int32_t *e2n_user, const PlanOptions 
     return OPF_OK;
 }
 
+void build_fixed(const Plan &P, int K, int NT, FixedLists &F)
+{
+    F = FixedLists();
+    F.K = K;
+    F.fine = K != P.cluster_size;
+    const int64_t nch = (P.N + K - 1) / K;
+    F.iblk.assign(2 * nch, 0);
+    F.cv_off.assign(nch + 1, 0);
+    if (!F.fine) {
+        for (int64_t c = 0; c < nch; ++c) {
+            F.iblk[2 * c] = P.cl_prim[2 * c];
+            F.iblk[2 * c + 1] = P.cl_nint[c];
+            F.cv_off[c + 1] = (int32_t)P.cl_cut_off[c + 1];
+        }
+    } else {
+        std::vector<int64_t> at(P.N + 1, 0);
+        for (int64_t k = 0; k < 2 * P.E; ++k) ++at[P.e2n[k] + 1];
+        for (int64_t i = 0; i < P.N; ++i) at[i + 1] += at[i];
+        for (int64_t c = 0; c < nch; ++c)
+            F.cv_off[c + 1] = (int32_t)at[std::min<int64_t>(P.N, (c + 1) * K)];
+        F.cv_eid.resize(2 * P.E);
+        F.cv_oth.resize(2 * P.E);
+        F.cv_own.resize(2 * P.E);
+        for (int64_t e = 0; e < P.E; ++e)
+            for (int h = 0; h < 2; ++h) {
+                const int32_t v = P.e2n[2 * e + h];
+                const int64_t s = at[v]++;
+                F.cv_eid[s] = (int32_t)e;
+                F.cv_oth[s] = (int32_t)((uint32_t)P.e2n[2 * e + 1 - h] | ((uint32_t)h << 31));
+                F.cv_own[s] = (uint16_t)(v % K);
+            }
+    }
+    F.rnd_off.assign(nch + 1, 0);
+    for (int64_t c = 0; c < nch; ++c) {
+        const int64_t n = (int64_t)F.iblk[2 * c + 1] + F.cv_off[c + 1] - F.cv_off[c];
+        F.rnd_off[c + 1] = F.rnd_off[c] + (int32_t)((n + NT - 1) / NT);
+    }
+    const int64_t nr = F.rnd_off[nch];
+    F.ent_base.assign(nr + 1, 0);
+    for (int64_t c = 0; c < nch; ++c) {
+        const int64_t ni = F.iblk[2 * c + 1], n = ni + F.cv_off[c + 1] - F.cv_off[c];
+        for (int64_t r = F.rnd_off[c], b = 0; b < n; ++r, b += NT) {
+            const int64_t e = std::min<int64_t>(n, b + NT);
+            F.ent_base[r + 1] = (int32_t)((e - b) + std::max<int64_t>(0, std::min(e, ni) - b));
+        }
+    }
+    for (int64_t r = 0; r < nr; ++r) F.ent_base[r + 1] += F.ent_base[r];
+    F.off.assign((size_t)nr * K, 0);
+    F.ent.resize(F.ent_base[nr]);
+    parallel_for(nch, [&](int64_t c) {
+        const int64_t i0 = F.iblk[2 * c], ni = F.iblk[2 * c + 1], s0 = F.cv_off[c];
+        const int64_t n = ni + F.cv_off[c + 1] - s0, v0 = c * K;
+        std::vector<uint16_t> fill(K + 1);
+        for (int64_t r = F.rnd_off[c], b = 0; b < n; ++r, b += NT) {
+            const int64_t e = std::min<int64_t>(n, b + NT);
+            uint32_t *off = &F.off[(size_t)r * K];
+            uint16_t *ent = F.ent.data() + F.ent_base[r];
+            auto visits = [&](const auto &see) {
+                for (int64_t k = b; k < e; ++k) {
+                    const int64_t s = s0 + k - ni;
+                    if (k < ni) {
+                        see(P.e2n[2 * (i0 + k)] - v0, k - b);
+                        see(P.e2n[2 * (i0 + k) + 1] - v0, (k - b) | 0x8000);
+                    } else if (F.fine) {
+                        see(F.cv_own[s], k - b);
+                    } else {
+                        see(P.e2n[2 * (int64_t)P.cl_cutf_eid[s] + P.cl_cutf_end[s]] - v0, k - b);
+                    }
+                }
+            };
+            std::fill(fill.begin(), fill.end(), 0);
+            visits([&](int64_t v, int64_t) { ++fill[v + 1]; });
+            for (int k = 0; k < K; ++k) fill[k + 1] = (uint16_t)(fill[k + 1] + fill[k]);
+            for (int k = 0; k < K; ++k) off[k] = fill[k] | ((uint32_t)fill[k + 1] << 16);
+            visits([&](int64_t v, int64_t entry) { ent[fill[v]++] = (uint16_t)entry; });
+        }
+    });
+}
+
 VerifyResult verify_plan(const Plan &P, const int32_t *e2n_user)
 {
     VerifyResult r;

@@ -112,6 +112,27 @@ struct Plan {
 int build_plan(int64_t N, int64_t E, const int32_t *e2n, const PlanOptions &opt, Plan &plan,
                std::string &err);
 
+// The fixed-order owner loop's lists (see gpu::FixedPlan): chunks of K
+// consecutive internal nodes, each with its visits (an interior block and cut
+// visits, as the owner kernel runs them) taken NT at a time, and per round and
+// node the slots of the round to add up, in visit order.
+struct FixedLists {
+    int32_t K = 0;
+    bool fine = false;  // chunks smaller than the owner clusters, visits of their own
+    std::vector<int32_t> iblk;               // [2 nchunk] (first edge, count); fine: zeros
+    std::vector<int32_t> cv_off, cv_eid, cv_oth;  // fine: every (edge, end) pair by owned node
+    std::vector<uint16_t> cv_own;
+    std::vector<int32_t> rnd_off;   // [nchunk+1] rounds of each chunk
+    std::vector<int32_t> ent_base;  // [rounds+1] first entry of each round
+    std::vector<uint32_t> off;      // [rounds][K] each node's entries in the round: first |
+                                    // past the last << 16
+    std::vector<uint16_t> ent;      // slot in the round, bit 15: the edge's second end
+};
+
+// Builds the lists over the plan's owner clusters (K = cluster_size), or, for
+// K < cluster_size, over chunks of K nodes with visits of their own.
+void build_fixed(const Plan &plan, int K, int NT, FixedLists &out);
+
 struct VerifyResult {
     bool ok = true;
     int property = 0;
