@@ -486,6 +486,19 @@ int opf_edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf
 int opf_edge_flux_stage_noalloc(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat n,
                                 opf_dat q0, opf_dat vol, opf_dat dt, opf_dat qout, double gamma,
                                 double alpha, double *ss_dev, void *stream);
+/* One five-stage iteration: stage k (0 .. 4) is the fused loop above from the
+ * state of stage k - 1 (stage 0: from q) with base state q and step alpha[k]
+ * (host array of 5), into qb (k even) or qc (k odd), so that the new state is
+ * left in qb; ss_dev (5 x 6 device doubles) is set to every stage's sums of
+ * res^2, which one launch forms for all stages.  variant OWNER (res < 0), or
+ * COLOURED, whose sums run in a fixed order (the same bits on every run): res
+ * then names a node dat (6, F64) whose values are added to the first stage's
+ * residual and which is zero afterwards, as the separate loops leave it.
+ * Errors: as opf_edge_flux_stage; OPF_EINVAL for another variant, or for
+ * COLOURED without a two-level colouring or with clusters above 512 nodes. */
+int opf_rk_iteration(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat n, opf_dat vol,
+                     opf_dat dt, opf_dat qb, opf_dat qc, opf_dat res, double gamma,
+                     const double *alpha, double *ss_dev, int variant, void *stream);
 int opf_geometry(opf_ctx *ctx, opf_set tets, opf_map t2n, opf_map t2e, opf_dat x, double period,
                  opf_dat w, opf_dat vol, int variant, void *stream);
 int opf_geometry_adjoint(opf_ctx *ctx, opf_set tets, opf_map t2n, opf_map t2e, opf_dat x,

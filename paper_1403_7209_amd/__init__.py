@@ -49,7 +49,7 @@ SYMBOLS = ("opf_init", "opf_finalize", "opf_last_error", "opf_set_allocator", "o
            "opf_decl_dat", "opf_par_loop", "opf_edge_flux", "opf_edge_flux_adjoint",
            "opf_edge_specrad", "opf_edge_gradient", "opf_edge_flux2", "opf_rk_stage",
            "opf_rk_stage_local", "opf_local_dt", "opf_dt_min", "opf_edge_flux_stage",
-           "opf_edge_flux_stage_noalloc", "opf_geometry",
+           "opf_edge_flux_stage_noalloc", "opf_rk_iteration", "opf_geometry",
            "opf_geometry_adjoint",
            "opf_sync", "opf_check_finite")
 
@@ -164,6 +164,8 @@ def load():
     lib.opf_edge_flux_stage.argtypes = [vp, i32, i32, i32, i32, i32, i32, i32, i32, d, d, vp, vp]
     lib.opf_edge_flux_stage_noalloc.argtypes = [vp, i32, i32, i32, i32, i32, i32, i32, i32, d, d,
                                                 vp, vp]
+    lib.opf_rk_iteration.argtypes = [vp, i32, i32, i32, i32, i32, i32, i32, i32, i32, d, P(d), vp,
+                                     ctypes.c_int, vp]
     lib.opf_geometry_adjoint.argtypes = [vp, i32, i32, i32, i32, d, i32, i32, i32, vp]
     lib.opf_sync.argtypes = [vp, vp]
     lib.opf_check_finite.argtypes = [vp, vp, ctypes.c_int, vp]
@@ -425,6 +427,16 @@ class Context:
                                                          _stream_ptr(stream, self.device)),
                     "opf_edge_flux_stage_noalloc")
 
+    def rk_iteration(self, edges, e2n, q, n, vol, qb, qc, alpha, ss, gamma=1.4, dt=-1, res=-1,
+                     variant=OWNER, stream=None):
+        """Five fused stages from q with steps alpha (5 floats), the new state in qb; ss
+        (5 x 6) = every stage's sum res^2.  variant OWNER, or COLOURED with res."""
+        a = (ctypes.c_double * 5)(*alpha)
+        self._check(self.lib.opf_rk_iteration(self._ctx, edges, e2n, q, n, vol, dt, qb, qc, res,
+                                              gamma, a, self._gbl_ptr(ss, 30, "ss"), variant,
+                                              _stream_ptr(stream, self.device)),
+                    "opf_rk_iteration")
+
     def geometry(self, tets, t2n, t2e, x, w, vol, period=1.0, variant=OWNER, stream=None,
                  access=INC):
         """w (edge dat, 3) and vol (node dat) += median-dual weights and volumes of the
@@ -503,7 +515,7 @@ class FluxProblem:
             if like.ctx is not ctx:
                 raise ValueError("like= must be a problem on the same context")
             for k in ("N", "E", "nodes", "edges", "e2n", "info", "node_new", "edge_new", "tets",
-                      "t2n", "t2e"):
+                      "t2n", "t2e", "cluster_size"):
                 setattr(self, k, getattr(like, k))
         else:
             e2n = np.ascontiguousarray(e2n, dtype=np.int32)
@@ -528,6 +540,7 @@ class FluxProblem:
                                  cluster_size=cluster_size, lane_groups=lane_groups,
                                  owner_compact=owner_compact, bank_spread=bank_spread,
                                  halo_order=halo_order)
+            self.cluster_size = cluster_size
             self.node_new = ctx.get_perm(self.nodes, self.N)
             self.edge_new = ctx.get_perm(self.edges, self.E)
         dev = ctx.torch_device
@@ -578,11 +591,29 @@ class FluxProblem:
         self.ctx.dt_min(self.nodes, self.vol, self.lam_d, cfl, self.dt_t, stream)
         return float(self.dt_t.item())
 
-    def _rk_fused(self, alpha_of_stage, dt_dat, stream):
-        """Five stages of the owner loop with the update fused in; stage k reads
-        the state of stage k-1 and writes the other of two stage buffers."""
+    def _fuses(self, variant):
+        """Whether an iteration of this variant has its stage updates fused into its
+        edge loops: OWNER; COLOURED where the plan has fixed-order lists."""
+        if variant == COLOURED:
+            return (self.info["coloured_ok"] and self.info["owner_ok"] and self.cluster_size <= 512
+                    and self._whole_ss())
+        return variant == OWNER
+
+    def _whole_ss(self):
+        return self.ss.shape == (5, 6) and self.ss.is_contiguous()
+
+    def _rk_fused(self, alpha_of_stage, dt_dat, variant, stream):
+        """Five stages of the edge loop with the update fused in; stage k reads the
+        state of stage k-1 and writes the other of two stage buffers."""
         if not hasattr(self, "qc"):
             self.qc = torch.empty_like(self.qa)
+        if self._whole_ss():
+            self.ctx.rk_iteration(self.edges, self.e2n, self.dat(self.qa, "qa"), self.w, self.vol,
+                                  self.dat(self.qb, "qb"), self.dat(self.qc, "qc"),
+                                  [float(alpha_of_stage(k)) for k in range(5)], self.ss, self.gamma,
+                                  dt_dat, self.res_d if variant == COLOURED else -1, variant, stream)
+            self.qa, self.qb = self.qb, self.qa
+            return
         qa = self.dat(self.qa, "qa")
         bufs = (self.dat(self.qb, "qb"), self.dat(self.qc, "qc"))
         self.ss.zero_()
@@ -598,10 +629,10 @@ class FluxProblem:
     def rk_iteration(self, dt, variant=COLOURED, stream=None, fused=True):
         """One 5-stage iteration; the new state is left in self.qa.  self.ss
         (5, 6) receives each stage's per-variable sum of squared residuals.
-        With the OWNER variant the stage update is fused into the edge loop
-        unless fused=False."""
-        if variant == OWNER and fused:
-            return self._rk_fused(lambda k: RK_ALPHA[k] * dt, -1, stream)
+        With the OWNER and COLOURED variants the stage update is fused into the
+        edge loop unless fused=False."""
+        if fused and self._fuses(variant):
+            return self._rk_fused(lambda k: RK_ALPHA[k] * dt, -1, variant, stream)
         qa, qb = self.dat(self.qa, "qa"), self.dat(self.qb, "qb")
         # the owner variant writes each residual once: no zeroing pass needed
         ra, rk = (WRITE, READ) if variant == OWNER else (INC, RW)
@@ -676,8 +707,8 @@ class FluxProblem:
     def rk_iteration_local(self, variant=COLOURED, stream=None, fused=True):
         """One 5-stage iteration with the per-node steps of the last
         compute_local_dt; otherwise as rk_iteration."""
-        if variant == OWNER and fused:
-            return self._rk_fused(lambda k: RK_ALPHA[k], self.dtl_d, stream)
+        if fused and self._fuses(variant):
+            return self._rk_fused(lambda k: RK_ALPHA[k], self.dtl_d, variant, stream)
         qa, qb = self.dat(self.qa, "qa"), self.dat(self.qb, "qb")
         ra, rk = (WRITE, READ) if variant == OWNER else (INC, RW)
         self.ss.zero_()

@@ -879,6 +879,7 @@ struct StagePtrs {
     const double *dt;  // per-node steps or null
     double adt;
     double *partial;   // [ncl][6]
+    double *res[6];    // fixed-order loop: added to the totals and cleared, or null
 };
 
 // HALVES: two workgroups per cluster, b and b + 8 of each 16 (dispatched to the
@@ -1147,9 +1148,10 @@ struct FixedPtrs {
 // barriers, and its wavefronts wait 80 % of their time (LDS pipe 30 % busy).
 // The owner kernel's atomics need no rounds and take 110 us on that mesh, but
 // their order varies.
-template <typename T, class Op, int KC>
+template <typename T, class Op, int KC, bool STAGE = false>
 __global__ __launch_bounds__(kOwnerThreads, (FixedTune<T, Op>::WAVES)) void k_edge_fixed(
-    OwnerPtrs p, FixedPtrs f, Arrays<T> a, T gamma, int N, int Kr, int ncl, int remap)
+    OwnerPtrs p, FixedPtrs f, Arrays<T> a, T gamma, int N, int Kr, int ncl, int remap, int overwrite,
+    StagePtrs<T> sp = {})
 {
     constexpr int NT = kOwnerThreads;
     using M = Message<Op>;
@@ -1246,12 +1248,41 @@ __global__ __launch_bounds__(kOwnerThreads, (FixedTune<T, Op>::WAVES)) void k_ed
             __syncthreads();
         }
     }
-    if (!sums) return;
+    const int g = v0 + node;
+    if constexpr (STAGE) {
+        double sq[NV];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        if (P > 1 && vb + i >= Op::NOUT) break;
-        double *y = a.y[vb + i];
-        st(y, v0 + node, ld(y, v0 + node) + acc[i]);
+        for (int i = 0; i < NV; ++i) sq[i] = 0.0;
+        if (sums) {
+            const double step = (sp.dt ? sp.adt * ld(sp.dt, g) : sp.adt) / ld(sp.vol, g);
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const int v = vb + i;
+                double r = acc[i];
+                if (sp.res[0]) {
+                    r += ld(sp.res[v], g);
+                    st(sp.res[v], g, 0.0);
+                }
+                sq[i] = r * r;
+                st(sp.q[v], g, (T)((double)ld(sp.q0[v], g) - step * r));
+            }
+        }
+        double *out = sp.partial + 6 * c;
+        if constexpr (P == 1) {
+            lds_sum6<NT>(sq, Y, out);
+        } else {
+            static_assert(NV == 1 && KC <= 64, "a sum's nodes are lanes of one wavefront");
+#pragma unroll
+            for (int o = KC / 2; o > 0; o >>= 1) sq[0] += __shfl_down(sq[0], o, KC);
+            if (sums && node == 0) out[vb] = sq[0];
+        }
+    } else if (sums) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (P > 1 && vb + i >= Op::NOUT) break;
+            double *y = a.y[vb + i];
+            st(y, g, overwrite ? acc[i] : ld(y, g) + acc[i]);
+        }
     }
 }
 
@@ -1296,19 +1327,24 @@ __global__ __launch_bounds__(kRkThreads) void k_local_dt(int N, const double *__
         dt[i] = cfl * vol[i] / lam[i];
 }
 
-// ss[0..5] += the sum of nparts rows of 6 partial sums (rows at buf +
-// kSumTail).  Workgroup g of kSumGroups sums the rows [g R, (g+1) R), each
-// thread a fixed stride of them, then through a fixed LDS tree, into
-// buf[6 g ..]; the last workgroup to finish adds the kSumGroups sums in
-// order.  Every order is fixed, so the result is the same on every run.
+// ss[0..5] += (overwrite: =) the sum of nparts rows of 6 partial sums (rows at
+// buf + kSumTail), for each of gridDim.y sets.  Workgroup g of the set's sums
+// the rows [g R, (g+1) R), each thread a fixed stride of them, then through a
+// fixed LDS tree, into buf[6 g ..]; the last workgroup to finish adds their sums
+// in order (a single one needs no hand-over).  Every order is fixed, so the
+// result is the same on every run.
 constexpr int kSumThreads = 256;
 
-__global__ __launch_bounds__(kSumThreads) void k_sum_partials(int nparts, double *buf, double *ss)
+__global__ __launch_bounds__(kSumThreads) void k_sum_partials(int nparts, double *buf0, double *ss0,
+                                                             int overwrite)
 {
+    double *buf = buf0 + (size_t)blockIdx.y * (kSumTail + 6 * (size_t)nparts);
+    double *ss = ss0 + 6 * blockIdx.y;
+    const int groups = (int)gridDim.x;
     const double *rows = buf + kSumTail;
     unsigned int *counter = reinterpret_cast<unsigned int *>(buf + 6 * kSumGroups);
     const int g = (int)blockIdx.x, t = (int)threadIdx.x;
-    const int per = (nparts + kSumGroups - 1) / kSumGroups;
+    const int per = (nparts + groups - 1) / groups;
     const int r0 = g * per, r1 = min(nparts, r0 + per);
     double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     constexpr int U = 4;  // rows whose loads are in flight together
@@ -1356,20 +1392,24 @@ __global__ __launch_bounds__(kSumThreads) void k_sum_partials(int nparts, double
         double s = 0.0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) s += red[t * kSumThreads + i];
-        buf[6 * g + t] = s;
+        if (groups == 1)
+            ss[t] = overwrite ? s : ss[t] + s;
+        else
+            buf[6 * g + t] = s;
     }
+    if (groups == 1) return;
     // publish this group's sums, then count it; the last group sees all
     __threadfence();
     __syncthreads();
-    if (t == 0) last = atomicAdd(counter, 1u) == (unsigned int)(kSumGroups - 1);
+    if (t == 0) last = atomicAdd(counter, 1u) == (unsigned int)(groups - 1);
     __syncthreads();
     if (!last) return;
     __threadfence();
     if (t < 6) {
         const volatile double *vb = buf;
         double s = 0.0;
-        for (int i = 0; i < kSumGroups; ++i) s += vb[6 * i + t];
-        ss[t] += s;
+        for (int i = 0; i < groups; ++i) s += vb[6 * i + t];
+        ss[t] = overwrite ? s : ss[t] + s;
     }
     if (t == 0) *counter = 0u;
 }
@@ -1560,37 +1600,42 @@ int run_owner(const DevPlan &P, const EdgeArrays &a, double gamma, hipStream_t s
 }
 
 template <typename T>
-int run_owner_stage(const DevPlan &P, const EdgeArrays &a, const NodeArrays &na, double gamma,
-                    double adt, double *ss, double *partial, hipStream_t st, const LaunchOpts &lo)
+StagePtrs<T> stage_ptrs(const NodeArrays &na, double adt, double *rows)
 {
-    if (!P.owner_ok || P.ncl <= 0 || !partial) return (int)hipErrorInvalidValue;
-    const size_t lds = owner_dyn_lds<T, OpFlux>(P.K);
-    const OwnerPtrs op = owner_ptrs(P, OwnerTune<T, OpFlux>::FOREIGN);
     StagePtrs<T> sp;
     for (int k = 0; k < 6; ++k) {
         sp.q0[k] = static_cast<const T *>(na.q0[k]);
         sp.q[k] = static_cast<T *>(na.q[k]);
+        sp.res[k] = na.res[k];
     }
     sp.vol = na.vol;
     sp.dt = na.dt;
     sp.adt = adt;
-    sp.partial = partial + kSumTail;
+    sp.partial = rows;
+    return sp;
+}
+
+template <typename T>
+int run_owner_stage(const DevPlan &P, const EdgeArrays &a, const StagePtrs<T> &sp, double gamma,
+                    hipStream_t st, const LaunchOpts &lo)
+{
+    if (!P.owner_ok || P.ncl <= 0) return (int)hipErrorInvalidValue;
+    const size_t lds = owner_dyn_lds<T, OpFlux>(P.K);
+    const OwnerPtrs op = owner_ptrs(P, OwnerTune<T, OpFlux>::FOREIGN);
     launch_owner<T, OpFlux, kOwnerThreads, true, false>(owner_streams<T, OpFlux>(P, true), P.ncl,
                                                         lds, st, op, typed<T>(a), (T)gamma, P, lo,
                                                         0, sp);
-    hipLaunchKernelGGL(k_sum_partials, dim3(kSumGroups), dim3(kSumThreads), 0, st, P.ncl, partial,
-                       ss);
     return (int)hipGetLastError();
 }
 
 // Chunk sizes fixed at compile time: the default cluster size and the small
 // meshes'.
-template <typename T, class Op, class F>
+template <typename T, class Op, bool STAGE = false, class F>
 void fixed_kernels(F &&f)
 {
-    f(512, k_edge_fixed<T, Op, 512>);
-    f(kFixedFine, k_edge_fixed<T, Op, kFixedFine>);
-    f(0, k_edge_fixed<T, Op, 0>);
+    f(512, k_edge_fixed<T, Op, 512, STAGE>);
+    f(kFixedFine, k_edge_fixed<T, Op, kFixedFine, STAGE>);
+    f(0, k_edge_fixed<T, Op, 0, STAGE>);
 }
 
 template <typename T, class Op>
@@ -1599,18 +1644,20 @@ size_t fixed_lds(int K)
     return stage_bytes<T, Op>(K) + (size_t)Message<Op>::NM * kOwnerThreads * sizeof(double);
 }
 
-template <typename T, class Op>
-int run_fixed(const DevPlan &P, const EdgeArrays &a, double gamma, hipStream_t st, const LaunchOpts &lo)
+template <typename T, class Op, bool STAGE = false>
+int run_fixed(const DevPlan &P, const EdgeArrays &a, double gamma, hipStream_t st, const LaunchOpts &lo,
+              const StagePtrs<T> &sp = {})
 {
     const FixedPlan &X = P.fixed;
+    if (X.K <= 0) return (int)hipErrorInvalidValue;
     const OwnerPtrs op{X.iblk, X.iw, X.cv_off, X.cv_eid, X.cv_oth, X.cv_own};
     const FixedPtrs fp{X.rnd_off, X.ent_base, X.off, X.ent};
     const size_t lds = fixed_lds<T, Op>(X.K);
     bool done = false;
-    fixed_kernels<T, Op>([&](int K, auto *kern) {
+    fixed_kernels<T, Op, STAGE>([&](int K, auto *kern) {
         if (done || (K != 0 && K != X.K)) return;
-        hipLaunchKernelGGL(kern, dim3(X.nchunk), dim3(kOwnerThreads), lds, st, op, fp,
-                           typed<T>(a), (T)gamma, P.N, X.K, X.nchunk, lo.xcd_remap);
+        hipLaunchKernelGGL(kern, dim3(X.nchunk), dim3(kOwnerThreads), lds, st, op, fp, typed<T>(a),
+                           (T)gamma, P.N, X.K, X.nchunk, lo.xcd_remap, lo.overwrite, sp);
         done = true;
     });
     return (int)hipGetLastError();
@@ -1620,10 +1667,9 @@ template <typename T, class Op>
 int run_edge(int variant, const DevPlan &P, const EdgeArrays &a, double gamma, hipStream_t st,
              const LaunchOpts &lo)
 {
+    if (lo.fixed) return run_fixed<T, Op>(P, a, gamma, st, lo);
     switch (variant) {
-    case V_COLOURED:
-        if (lo.fixed) return run_fixed<T, Op>(P, a, gamma, st, lo);
-        return run_coloured_bs<T, Op, false>(P, a, gamma, st, lo);
+    case V_COLOURED: return run_coloured_bs<T, Op, false>(P, a, gamma, st, lo);
     case V_COLOURED_LDS_ATOMIC: return run_coloured_bs<T, Op, true>(P, a, gamma, st, lo);
     case V_ATOMIC: return run_atomic<T, Op>(P, a, gamma, st, lo);
     case V_OWNER: return run_owner<T, Op>(P, a, gamma, st, lo);
@@ -1693,6 +1739,9 @@ int raise_all(size_t bytes)
     if (!rc) rc = raise_owner<T, O, NT, false, H>(bytes);
     if constexpr (std::is_same<Op, OpFlux>::value) {
         if (!rc) rc = raise_owner<T, Op, kOwnerThreads, true, false>(bytes);
+        fixed_kernels<T, Op, true>([&](int, auto *kern) {
+            if (!rc) rc = raise_one(reinterpret_cast<const void *>(kern), bytes);
+        });
     }
     return rc;
 }
@@ -1772,12 +1821,29 @@ int launch_edge(int op, bool fp32, int variant, const DevPlan &P, const EdgeArra
     }
 }
 
-int launch_edge_stage(bool fp32, const DevPlan &P, const EdgeArrays &a, const NodeArrays &na,
-                      double gamma, double adt, double *ss, double *partial, hipStream_t st,
-                      const LaunchOpts &lo)
+template <typename T>
+static int run_stage(const DevPlan &P, const EdgeArrays &a, const NodeArrays &na, double gamma,
+                     double adt, double *rows, hipStream_t st, const LaunchOpts &lo)
 {
-    return fp32 ? run_owner_stage<float>(P, a, na, gamma, adt, ss, partial, st, lo)
-                : run_owner_stage<double>(P, a, na, gamma, adt, ss, partial, st, lo);
+    if (!rows) return (int)hipErrorInvalidValue;
+    const StagePtrs<T> sp = stage_ptrs<T>(na, adt, rows);
+    if (lo.fixed) return run_fixed<T, OpFlux, true>(P, a, gamma, st, lo, sp);
+    return run_owner_stage<T>(P, a, sp, gamma, st, lo);
+}
+
+int launch_edge_stage(bool fp32, const DevPlan &P, const EdgeArrays &a, const NodeArrays &na,
+                      double gamma, double adt, double *rows, hipStream_t st, const LaunchOpts &lo)
+{
+    return fp32 ? run_stage<float>(P, a, na, gamma, adt, rows, st, lo)
+                : run_stage<double>(P, a, na, gamma, adt, rows, st, lo);
+}
+
+int launch_sum_partials(int nrows, int nsets, double *buf, double *ss, bool overwrite, hipStream_t st)
+{
+    const int groups = nrows <= kSumAlone ? 1 : kSumGroups;
+    hipLaunchKernelGGL(k_sum_partials, dim3(groups, nsets), dim3(kSumThreads), 0, st, nrows, buf, ss,
+                       overwrite ? 1 : 0);
+    return (int)hipGetLastError();
 }
 
 int static_scratch_address(double **out)
@@ -1804,9 +1870,8 @@ static int run_rk(int N, const NodeArrays &a, double alpha_dt, double *ss, doubl
     const int grid = std::min(kRkBlocks, std::max(1, (N + kRkThreads - 1) / kRkThreads));
     hipLaunchKernelGGL((k_rk_stage<T>), dim3(grid), dim3(kRkThreads), 0, st, N, p, alpha_dt,
                        partial + kSumTail, keep_res ? 1 : 0);
-    hipLaunchKernelGGL(k_sum_partials, dim3(kSumGroups), dim3(kSumThreads), 0, st, grid, partial,
-                       ss);
-    return (int)hipGetLastError();
+    const int e = (int)hipGetLastError();
+    return e ? e : launch_sum_partials(grid, 1, partial, ss, false, st);
 }
 
 int launch_rk_stage(bool fp32, int N, const NodeArrays &a, double alpha_dt, double *ss,

@@ -28,6 +28,7 @@ constexpr int kOwnerThreads = 512;
 // set when the node is the second end of an interior edge.
 struct FixedPlan {
     int K = 0, nchunk = 0;  // K = 0: no lists
+    bool fine = false;      // chunks smaller than the owner clusters
     const int2 *iblk = nullptr;
     const uint32_t *iw = nullptr;
     const int *cv_off = nullptr, *cv_eid = nullptr, *cv_oth = nullptr;
@@ -41,6 +42,8 @@ constexpr int kFixedMaxK = kOwnerThreads;
 // The chunk of a small mesh, and the most nodes of one (see fixed_chunk).
 constexpr int kFixedFine = 32;
 constexpr int kFixedFineNodes = 65536;
+// Stages of one iteration.
+constexpr int kStages = 5;
 
 // Device copy of an execution plan (internal numbering, int32 offsets).
 struct DevPlan {
@@ -74,7 +77,9 @@ struct DevPlan {
     const uint16_t *cvf_own = nullptr;
     FixedPlan fixed;
     // flat colouring: colour c runs edges flat_eid[flat_off[c] .. flat_off[c+1])
-    double *stage_partial = nullptr;  // kSumTail + [ncl][6]: partial sums of the fused stage
+    // partial sums of the fused stages: per stage of an iteration kSumTail + 6
+    // doubles per cluster or chunk
+    double *stage_partial = nullptr;
     int nflat = 0;
     std::vector<int64_t> flat_off;  // host copy [nflat+1]
     const int *flat_eid = nullptr;  // [E]
@@ -92,7 +97,7 @@ struct EdgeArrays {
 struct LaunchOpts {
     int xcd_remap = 1;  // give each XCD a contiguous range of partitions/clusters
     int overwrite = 0;  // owner variant: res = sum instead of res += sum
-    int fixed = 0;      // coloured variant: through the plan's fixed-order lists
+    int fixed = 0;      // coloured and owner variants: through the plan's fixed-order lists
 };
 
 // Returns 0 or a hipError_t value.
@@ -108,13 +113,14 @@ struct NodeArrays {
 };
 
 // Buffers of partial sums (the stage reductions): kSumTail doubles, then 6
-// per row.  The second pass sums the rows in kSumGroups workgroups, each over
-// a fixed block of rows in a fixed order, into the first 6 * kSumGroups
-// doubles; the last workgroup to finish (a counter in the next word) adds
+// per row.  The second pass sums up to kSumAlone rows in one workgroup, more in
+// kSumGroups, each over a fixed block of rows in a fixed order, into the first
+// 6 * kSumGroups doubles; the last workgroup to finish (a counter in the next word) adds
 // those in order.  The counter must be zero before the first use of a buffer
 // and is zero again after every pass.
 constexpr int kSumGroups = 16;
 constexpr int kSumTail = 6 * kSumGroups + 2;
+constexpr int kSumAlone = 1024;
 
 // q = q0 - alpha_dt * res / vol (alpha_dt * dt_i with per-node steps),
 // ss[v] += sum res^2 (two passes, deterministic), res = 0 unless keep_res.
@@ -124,15 +130,20 @@ constexpr int kRkBlocks = 2048;
 int launch_rk_stage(bool fp32, int N, const NodeArrays &a, double alpha_dt, double *ss,
                     double *partial, bool keep_res, hipStream_t stream);
 
-// The owner FP64/FP32 edge-flux loop with the stage update fused into it:
-// q = q0 - adt * res / vol (adt * dt_i when a.dt is set) for every node, and
-// ss[v] += sum res^2 (per-cluster partials, fixed-order second pass); the
-// residual is never written.  The plan must have owner clusters.  `partial`
-// holds kSumTail + 6 * P.ncl doubles (counter zero); every cluster writes its
-// six before they are summed.
+// The FP64/FP32 edge-flux loop with the stage update fused into it: q = q0 -
+// adt * res / vol (adt * dt_i when a.dt is set) for every node, and the sums of
+// res^2 per component of each cluster (lo.fixed: chunk) to rows[6 k ..]; the
+// residual is never written.  With a.res set (lo.fixed only) the total is added
+// to what it holds and it is cleared.  The plan must have owner clusters.
 int launch_edge_stage(bool fp32, const DevPlan &P, const EdgeArrays &a, const NodeArrays &na,
-                      double gamma, double adt, double *ss, double *partial, hipStream_t stream,
+                      double gamma, double adt, double *rows, hipStream_t stream,
                       const LaunchOpts &lo);
+
+// The second pass over `nsets` buffers of partial sums (kSumTail + 6 nrows
+// doubles each, one after the other): ss[6 k + v] += the sums of set k, or = with
+// overwrite.
+int launch_sum_partials(int nrows, int nsets, double *buf, double *ss, bool overwrite,
+                        hipStream_t stream);
 
 // Clusters whose partial sums fit the library's static device scratch (the
 // fused stage for callers that cannot allocate): 6 doubles each, 768 KiB,

@@ -229,7 +229,8 @@ int fixed_chunk(const opf::Plan &P)
     const int K = P.cluster_size;
     if (K <= 0 || K > opf::gpu::kFixedMaxK) return 0;
     const bool fine = P.N > K && K > opf::gpu::kFixedFine && P.N <= opf::gpu::kFixedFineNodes;
-    return fine ? opf::gpu::kFixedFine : K;
+    if (fine) return opf::gpu::kFixedFine;
+    return P.coloured_ok ? K : 0;
 }
 
 // The fixed-order loop's arrays (see FixedPlan).
@@ -262,6 +263,7 @@ int upload_fixed(opf_ctx *ctx, PlanRec &pr)
     if (!rc) rc = upload(ctx, pr, F.off, X.off);
     if (!rc) rc = upload(ctx, pr, F.ent, X.ent);
     X.K = K;
+    X.fine = F.fine;
     X.nchunk = (int)(F.rnd_off.size() - 1);
     return rc;
 }
@@ -300,9 +302,10 @@ int upload_plan(opf_ctx *ctx, PlanRec &pr)
     if (D.owner_ok) {
         if (P.cluster_size > 8192) return ctx->fail(OPF_EINVAL, "cluster_size above 8192");
         rc = upload_owner(ctx, pr);
-        if (!rc && P.coloured_ok) rc = upload_fixed(ctx, pr);
+        if (!rc) rc = upload_fixed(ctx, pr);
         if (!rc) {
-            const size_t nb = sizeof(double) * (opf::gpu::kSumTail + 6 * (size_t)D.ncl);
+            const size_t rows = (size_t)std::max(D.ncl, D.fixed.nchunk);
+            const size_t nb = sizeof(double) * opf::gpu::kStages * (opf::gpu::kSumTail + 6 * rows);
             D.stage_partial = static_cast<double *>(ctx->dalloc(nb));
             if (!D.stage_partial) {
                 rc = ctx->fail(OPF_ENOMEM, "device allocation of plan arrays failed");
@@ -511,6 +514,17 @@ int check_gbl_disjoint(opf_ctx *ctx, const void *p, size_t bytes, std::initializ
     return OPF_OK;
 }
 
+// Whether a loop of this variant runs over the plan's fixed-order lists: the
+// coloured variant wherever there are any (the same fixed order on every run,
+// without a launch per partition colour); the owner variant on a small mesh,
+// whose clusters would leave most CUs idle.
+bool takes_fixed(const PlanRec &pr, int variant)
+{
+    const opf::gpu::FixedPlan &X = pr.dev.fixed;
+    if (variant == OPF_V_COLOURED) return X.K > 0;
+    return variant == OPF_V_OWNER && X.fine;
+}
+
 int edge_loop(opf_ctx *ctx, int kernel, opf_set s, int nargs, const opf_arg *args, int ngbl,
               const opf_gbl *gbls, int variant, hipStream_t st)
 {
@@ -634,7 +648,7 @@ int edge_loop(opf_ctx *ctx, int kernel, opf_set s, int nargs, const opf_arg *arg
         if (lds > ctx->max_lds)
             return ctx->fail(OPF_EINVAL, "a workgroup needs " + std::to_string(lds) +
                                              " B of LDS; use a smaller block or cluster size");
-        if (variant == OPF_V_COLOURED && pr.dev.fixed.K > 0) {
+        if (takes_fixed(pr, variant)) {
             const size_t fl = opf::gpu::fixed_lds_bytes(op, fp32, pr.dev.fixed.K);
             lo.fixed = fl <= ctx->max_lds ? 1 : 0;
             if (lo.fixed) lds = fl;
@@ -1685,15 +1699,31 @@ int opf_edge_flux2(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat 
 
 namespace {
 
-// The fused edge loop + stage.  noalloc: the per-cluster partials go to the
-// static device scratch of the current device instead of the plan's buffer, and
-// nothing is allocated (no context scratch, no event): the allocation-free entry
-// point.
+// How a fused stage runs.
+struct StageHow {
+    // the partials go to the static device scratch of the current device instead
+    // of the plan's buffer, and nothing is allocated (no context scratch, no
+    // event): the allocation-free entry point
+    bool noalloc = false;
+    int variant = OPF_V_OWNER;
+    // a stage of an iteration: its partials go to set `set` of the plan's buffer,
+    // and the caller orders the scratch and sums all sets at the end
+    int set = -1;
+    opf_dat res = -1;  // coloured: a residual to add to the total and clear
+};
+
+int stage_rows(const PlanRec &pr, int variant)
+{
+    return takes_fixed(pr, variant) ? pr.dev.fixed.nchunk : pr.dev.ncl;
+}
+
+// The fused edge loop + stage.
 int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat n, opf_dat q0,
                     opf_dat vol, opf_dat dt, opf_dat qout, double gamma, double alpha,
-                    double *ss_dev, void *stream, bool noalloc)
+                    double *ss_dev, void *stream, const StageHow &how)
 {
     if (!ctx) return OPF_EINVAL;
+    const bool noalloc = how.noalloc;
     ctx->err.clear();
     if (!ctx->set_ok(edges) || !ctx->map_ok(e2n)) return ctx->fail(OPF_EINVAL, "invalid handle");
     const MapRec &mr = ctx->maps[e2n];
@@ -1717,11 +1747,17 @@ int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat
         rc = check_arg(ctx, a[k], w[k], k);
     }
     if (rc) return rc;
+    if (how.res >= 0) {
+        const opf_arg ra = {how.res, 0, e2n, 6, OPF_F64, OPF_INC};
+        rc = check_arg(ctx, ra, Want{nodes, 0, e2n, 6, OPF_F64, OPF_INC}, 7);
+        if (rc) return rc;
+    }
     if (qout == q || qout == q0) return ctx->fail(OPF_EINVAL, "qout must not alias q or q0");
     if (!ss_dev) return ctx->fail(OPF_EINVAL, "ss must be device memory");
-    rc = check_disjoint(ctx, qout, {q, n, q0, vol, dt}, "fused stage qout");
+    rc = check_disjoint(ctx, qout, {q, n, q0, vol, dt, how.res}, "fused stage qout");
+    if (!rc && how.res >= 0) rc = check_disjoint(ctx, how.res, {q, n, q0, vol, dt}, "fused stage res");
     if (!rc)
-        rc = check_gbl_disjoint(ctx, ss_dev, 6 * sizeof(double), {q, n, q0, vol, dt, qout},
+        rc = check_gbl_disjoint(ctx, ss_dev, 6 * sizeof(double), {q, n, q0, vol, dt, qout, how.res},
                                 "fused stage ss");
     if (rc) return rc;
     auto it = ctx->plans.find(e2n);
@@ -1744,10 +1780,12 @@ int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat
     }
     if (!pr.on_device) return ctx->fail(OPF_ESTATE, "plan is not on the device");
     const bool fp32 = T == OPF_F32;
-    const size_t lds = opf::gpu::edge_lds_bytes(opf::gpu::OP_FLUX, fp32, OPF_V_OWNER, pr.dev.umax,
-                                                pr.dev.K);
+    size_t lds = opf::gpu::edge_lds_bytes(opf::gpu::OP_FLUX, fp32, how.variant, pr.dev.umax, pr.dev.K);
     if (lds > ctx->max_lds)
         return ctx->fail(OPF_EINVAL, "a workgroup needs " + std::to_string(lds) + " B of LDS");
+    opf::gpu::LaunchOpts lo;
+    lo.fixed = takes_fixed(pr, how.variant) ? 1 : 0;
+    if (lo.fixed) lds = opf::gpu::fixed_lds_bytes(opf::gpu::OP_FLUX, fp32, pr.dev.fixed.K);
     if (lds > ctx->lds_limit) {
         int e = opf::gpu::set_lds_limit(ctx->max_lds);
         if (e) return hip_fail(ctx, (hipError_t)e, "raising the LDS limit");
@@ -1765,18 +1803,23 @@ int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat
     }
     na.vol = static_cast<const double *>(ctx->dats[vol].ptr);
     if (dt >= 0) na.dt = static_cast<const double *>(ctx->dats[dt].ptr);
-    opf::gpu::LaunchOpts lo;
+    if (how.res >= 0)
+        for (int c = 0; c < 6; ++c) na.res[c] = (double *)comp(ctx->dats[how.res], c);
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    if (noalloc) {
-        const int e = opf::gpu::launch_edge_stage(fp32, pr.dev, ea, na, gamma, alpha, ss_dev,
-                                                  partial, st, lo);
+    const int rows = stage_rows(pr, how.variant);
+    if (how.set >= 0) {
+        partial += (size_t)how.set * (opf::gpu::kSumTail + 6 * (size_t)rows);
+        const int e = opf::gpu::launch_edge_stage(fp32, pr.dev, ea, na, gamma, alpha,
+                                                  partial + opf::gpu::kSumTail, st, lo);
         return e ? hip_fail(ctx, (hipError_t)e, "fused loop launch") : OPF_OK;
     }
-    rc = scratch_begin(ctx, st);
+    if (!noalloc) rc = scratch_begin(ctx, st);
     if (rc) return rc;
-    int e = opf::gpu::launch_edge_stage(fp32, pr.dev, ea, na, gamma, alpha, ss_dev, partial, st, lo);
+    int e = opf::gpu::launch_edge_stage(fp32, pr.dev, ea, na, gamma, alpha,
+                                        partial + opf::gpu::kSumTail, st, lo);
+    if (!e) e = opf::gpu::launch_sum_partials(rows, 1, partial, ss_dev, false, st);
     if (e) return hip_fail(ctx, (hipError_t)e, "fused loop launch");
-    return scratch_end(ctx, st);
+    return noalloc ? OPF_OK : scratch_end(ctx, st);
 }
 
 }  // namespace
@@ -1788,15 +1831,66 @@ int opf_edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf
                         double alpha, double *ss_dev, void *stream)
 {
     return edge_flux_stage(ctx, edges, e2n, q, n, q0, vol, dt, qout, gamma, alpha, ss_dev, stream,
-                           false);
+                           StageHow());
 }
 
 int opf_edge_flux_stage_noalloc(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat n,
                                 opf_dat q0, opf_dat vol, opf_dat dt, opf_dat qout, double gamma,
                                 double alpha, double *ss_dev, void *stream)
 {
-    return edge_flux_stage(ctx, edges, e2n, q, n, q0, vol, dt, qout, gamma, alpha, ss_dev, stream,
-                           true);
+    StageHow how;
+    how.noalloc = true;
+    return edge_flux_stage(ctx, edges, e2n, q, n, q0, vol, dt, qout, gamma, alpha, ss_dev, stream, how);
+}
+
+int opf_rk_iteration(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat n, opf_dat vol,
+                     opf_dat dt, opf_dat qb, opf_dat qc, opf_dat res, double gamma,
+                     const double *alpha, double *ss_dev, int variant, void *stream)
+{
+    if (!ctx) return OPF_EINVAL;
+    ctx->err.clear();
+    constexpr int S = opf::gpu::kStages;
+    if (!alpha || !ss_dev) return ctx->fail(OPF_EINVAL, "alpha and ss must not be NULL");
+    if (variant != OPF_V_OWNER && variant != OPF_V_COLOURED)
+        return ctx->fail(OPF_EINVAL, "the iteration runs as OWNER or COLOURED");
+    if ((res >= 0) != (variant == OPF_V_COLOURED))
+        return ctx->fail(OPF_EINVAL, "the COLOURED iteration takes a residual, the OWNER one none");
+    if (!ctx->dat_ok(qb) || !ctx->dat_ok(qc)) return ctx->fail(OPF_EINVAL, "invalid dat handle");
+    int rc = check_gbl_disjoint(ctx, ss_dev, 6 * S * sizeof(double), {q, n, vol, dt, qb, qc, res},
+                                "iteration ss");
+    if (!rc) rc = check_disjoint(ctx, qc, {q, qb, n, vol, dt, res}, "iteration qc");
+    if (rc) return rc;
+    auto it = ctx->plans.find(e2n);
+    if (it == ctx->plans.end()) return ctx->fail(OPF_ESTATE, "no plan for this map: call opf_plan");
+    if (variant == OPF_V_COLOURED && (!it->second->host.coloured_ok || !takes_fixed(*it->second, variant)))
+        return ctx->fail(OPF_EINVAL, "the plan has no fixed-order lists (a two-level colouring and "
+                                     "clusters of at most 512 nodes are needed)");
+    rc = device_ready(ctx);
+    if (rc) return rc;
+    const hipStream_t st = static_cast<hipStream_t>(stream);
+    rc = scratch_begin(ctx, st);
+    if (rc) return rc;
+    StageHow how;
+    how.variant = variant;
+    opf_dat src = q;
+    for (int k = 0; k < S && !rc; ++k) {
+        const opf_dat dst = k % 2 ? qc : qb;
+        how.set = k;
+        how.res = k == 0 ? res : -1;
+        rc = edge_flux_stage(ctx, edges, e2n, src, n, q, vol, dt, dst, gamma, alpha[k], ss_dev + 6 * k,
+                             stream, how);
+        src = dst;
+    }
+    if (!rc) {
+        const PlanRec &pr = *it->second;
+        const int e = opf::gpu::launch_sum_partials(stage_rows(pr, variant), S, pr.dev.stage_partial,
+                                                    ss_dev, true, st);
+        if (e) rc = hip_fail(ctx, (hipError_t)e, "iteration launch");
+    }
+    const std::string why = ctx->err;
+    const int re = scratch_end(ctx, st);
+    if (rc) return ctx->fail(rc, why);
+    return re;
 }
 
 int opf_geometry(opf_ctx *ctx, opf_set tets, opf_map t2n, opf_map t2e, opf_dat x, double period,

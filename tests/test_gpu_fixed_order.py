@@ -1,7 +1,9 @@
-"""The fixed-order edge loop (coloured variant) against the oracle, at the edges of
-its chunks: meshes of fewer nodes than a chunk, of one chunk more, with a last
-chunk of one node, at both sides of the small-mesh limit (65,536 nodes), cluster
-sizes with and without a compile-time instance.  Results must be the same bits on every run."""
+"""The fixed-order edge loop (coloured variant, and every loop of a small mesh's
+owner variant) against the oracle, at the edges of its chunks and rounds:
+meshes of fewer nodes than a chunk, of one chunk more, with a last chunk of one
+node, at both sides of the small-mesh limit (65,536 nodes), cluster sizes with
+and without a compile-time instance, and a node with more edges than a round
+has visits.  Results must be the same bits on every run."""
 import numpy as np
 import pytest
 import torch
@@ -37,6 +39,12 @@ def chain(N):  # every node to its next and its next but two
     return Graph(N, e)
 
 
+def star(N):  # node 0 in every edge, the orientation alternating
+    e = np.stack([np.zeros(N - 1, int), np.arange(1, N)], 1)
+    e[::2] = e[::2, ::-1]
+    return Graph(N, e)
+
+
 def box(n):
     m = meshgen.build_mesh(n, 0, 0.2)
     g = Graph(m.N, m.e2n)
@@ -46,14 +54,16 @@ def box(n):
 
 CASES = {  # graph, cluster size, variants
     "one-chunk": (lambda: box(6), 512, (pk.COLOURED,)),
-    "fine-513": (lambda: chain(513), 512, (pk.COLOURED,)),
-    "fine-33-of-64": (lambda: chain(65), 64, (pk.COLOURED,)),
-    "fine-box11": (lambda: box(11), 512, (pk.COLOURED,)),
-    "fine-limit": (lambda: chain(65536), 512, (pk.COLOURED,)),
+    "fine-513": (lambda: chain(513), 512, (pk.COLOURED, pk.OWNER)),
+    "fine-33-of-64": (lambda: chain(65), 64, (pk.COLOURED, pk.OWNER)),
+    "fine-box11": (lambda: box(11), 512, (pk.COLOURED, pk.OWNER)),
+    "fine-limit": (lambda: chain(65536), 512, (pk.COLOURED, pk.OWNER)),
     "above-limit": (lambda: chain(65537), 512, (pk.COLOURED,)),
     "run-time-chunk": (lambda: chain(65537), 200, (pk.COLOURED,)),
     "box41-of-64": (lambda: box(41), 64, (pk.COLOURED,)),
     "box41": (lambda: box(41), 512, (pk.COLOURED,)),
+    # no two-level colouring: only the owner variant
+    "star": (lambda: star(1500), 512, (pk.OWNER,)),
 }
 
 
@@ -104,3 +114,40 @@ def test_loops_and_iteration(name):
         assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
         assert close(p, out[0][0], q1)
         assert normwise(out[0][1].cpu().numpy().T, ss1.T) <= TOL
+        if v == pk.OWNER:  # WRITE overwrites
+            r = torch.full((6, g.N), 1e30, **f64)
+            p.residual(p.qa, r, v, res_access=pk.WRITE)
+            ctx.sync()
+            assert close(p, r, res)
+
+
+def test_coloured_iteration_takes_up_the_residual():
+    """What p.res holds enters the first stage, and p.res is zero afterwards, fused or not."""
+    g = box(9)
+    ctx = pk.Context(DEV)
+    p = pk.FluxProblem(ctx, g.e2n, g.w, g.vol, g.q)
+    q0, src = p.qa.clone(), torch.randn(6, g.N, dtype=torch.float64, device=DEV)
+    out = []
+    for fused in (False, True):
+        p.qa.copy_(q0)
+        p.res.copy_(src)
+        p.rk_iteration(1e-4, fused=fused)
+        ctx.sync()
+        out.append((p.qa.cpu().numpy(), p.ss.cpu().numpy()))
+        assert not p.res.any()
+    assert normwise(out[1][0], out[0][0]) <= TOL and normwise(out[1][1].T, out[0][1].T) <= TOL
+
+
+def test_coloured_iteration_fp32_and_local_steps():
+    g = box(9)
+    ctx = pk.Context(DEV)
+    for fp32, tol in ((False, TOL), (True, 1e-5)):
+        p = pk.FluxProblem(ctx, g.e2n, g.w, g.vol, g.q, fp32=fp32)
+        q0, out = p.qa.clone(), []
+        for fused in (False, True):
+            p.qa.copy_(q0)
+            p.compute_local_dt()
+            p.rk_iteration_local(fused=fused)
+            ctx.sync()
+            out.append((p.qa.double().cpu().numpy(), p.ss.cpu().numpy()))
+        assert normwise(out[1][0], out[0][0]) <= tol and normwise(out[1][1].T, out[0][1].T) <= tol
