@@ -14,10 +14,11 @@
 // volume quarters (or, in reverse, its four x-bar shares) to HBM with FP64
 // atomics.  Gather: no atomics, fixed summation orders, the same bits on every
 // run.  The forward gather walks the tets around each edge from coordinates
-// staged in LDS (ring form, below); the reverse (and the forward, where a
-// mesh does not fit the ring form) writes per-tet results to a scratch buffer
-// that one thread per edge or node then sums over its incident tets.  The
-// loop runs once per mesh (or once per design step for the reverse).
+// staged in LDS (ring form, below), the gather reverse the edges around each
+// node (link form, at the end).  Where a mesh does not fit them, per-tet results
+// go to a scratch buffer that one thread per edge or node then sums over its
+// incident tets.  The loop runs once per mesh (or once per design step for the
+// reverse).
 #include <hip/hip_runtime.h>
 
 #include "kernels.hpp"
@@ -540,6 +541,172 @@ __global__ __launch_bounds__(kGeoVolThreads) void k_geo_vol(TetArrays a)
     }
 }
 
+// ------------------------------------------------------------ link form -- */
+//
+// The reverse without per-tet records.  Where the tets around edge (a, b) close
+// a ring, its weight is the sum of c_(i-1) x c_i / 12 over the ring (the terms
+// in a and b cancel), so only the ring's vertices see it: vertex c_i gets
+// wbar x (c_(i-1) - c_(i+1)) / 12.  A node thus sums over the edges of its link
+// (the edges in whose ring it stands, 36 on average) the edge's adjoint crossed
+// with the difference of the two vertices next to it.  Those two, r and s, are
+// also the apexes of the two tets (a, b, r, v) and (a, b, v, s) on the two sides
+// of the triangle (a, b, v), whose volumes change with v by (a x b + b x r +
+// r x a) / 6 and -(a x b + b x s + s x a) / 6 (all from v); a tet's volume
+// adjoint is a quarter of the sum over its vertices, so the a x b terms of the
+// two add up to (volbar_r - volbar_s) / 24 (a x b), and the other terms are
+// those of the tets' other link edges.  One workgroup per chunk stages the
+// coordinates, volume adjoints and edge adjoints its nodes need in LDS, then
+// kLinkSplit threads per node walk its entries and add their sums in a fixed
+// order: the same bits on every run.
+// Against per-tet records (every tet's shares written, then summed per node:
+// 11.7 GB moved on the 160^3 box for 1.8 GB it needs) the 1M-node box takes 237 us
+// instead of 730.  What bounds it now is the staging: 20 cache lines per node
+// go from L2 to the CUs (2.5 GB, about 10 TB/s), since a chunk's edges share
+// their lines with those of its neighbours; without the edge adjoints it takes
+// 190 us, without the walk 225.  Larger chunks (76 KB of LDS, two workgroups per
+// CU) and smaller ones (38 KB, four) are 1-3 % slower; 512-node chunks that take
+// their edges in slices of 1024 halve those lines but wait at each slice
+// (718 us).  All loads are issued before the first wait: one dependent trip each
+// for offsets, indices and data.
+constexpr int kLinkAhead = 10;  // entries of a thread fetched before the staging
+constexpr int kLinkBatch = 4;   // edge adjoints of a thread in flight together
+
+template <bool WRAP, bool VOL>
+__device__ __forceinline__ void link_walk(const TetArrays &a, const double2 *XY, const double2 *ZV,
+                                          const double2 *W01, const double *W2, int e0, int v, int j0,
+                                          int j1, const uint32_t (&pre)[kLinkAhead], double period,
+                                          double (&out)[3])
+{
+    const double ip = WRAP ? 1.0 / period : 0.0;
+    const double2 vxy = XY[v], vzv = ZV[v];
+    const double xv[3] = {vxy.x, vxy.y, vzv.x};
+    // row l relative to v
+    auto from_v = [&](uint32_t l, double *d, double &vb) {
+        const double2 xy = XY[l], zv = ZV[l];
+        const double x[3] = {xy.x, xy.y, zv.x};
+        geo_diff(x, xv, WRAP, period, ip, d);
+        vb = zv.y;
+    };
+    double sw[3] = {0.0, 0.0, 0.0}, sv[3] = {0.0, 0.0, 0.0};
+    auto entry = [&](uint32_t en) {
+        const uint32_t slot = en & 0xfffu;
+        const double2 w01 = W01[slot];
+        const double wb[3] = {w01.x, w01.y, W2[slot]};
+        double dr[3], ds[3], d[3], c[3], vr, vs;
+        from_v((en >> 12) & 0x3ffu, dr, vr);
+        from_v(en >> 22, ds, vs);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) d[k] = dr[k] - ds[k];
+        cross3(wb, d, c);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) sw[k] += c[k];
+        if constexpr (VOL) {
+            const uint32_t ab = a.lk_ends[e0 + slot];
+            double da[3], db[3], un;
+            from_v(ab & 0xffffu, da, un);
+            from_v(ab >> 16, db, un);
+            cross3(da, db, c);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) sv[k] += (vr - vs) * c[k];
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < kLinkAhead; ++i)
+        if (j0 + i * kLinkSplit < j1) entry(pre[i]);
+    for (int j = j0 + kLinkAhead * kLinkSplit; j < j1; j += kLinkSplit) entry(a.lk_ent[j]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        out[k] = sw[k] * (1.0 / 12.0);
+        if constexpr (VOL) out[k] += sv[k] * (1.0 / 24.0);
+    }
+}
+
+__global__ __launch_bounds__(kLinkThreads, 6) void k_link_reverse(TetArrays a, double period)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int c = xcd_map((int)blockIdx.x, (int)gridDim.x), t = (int)threadIdx.x;
+    const int v0 = a.lk_node[c], nown = a.lk_node[c + 1] - v0;
+    const int h0 = a.lk_halo_off[c], rows = nown + a.lk_halo_off[c + 1] - h0;
+    const int e0 = a.lk_edge_off[c], ne = a.lk_edge_off[c + 1] - e0;
+    double2 *XY = reinterpret_cast<double2 *>(smem), *ZV = XY + rows, *W01 = ZV + rows;
+    double *W2 = reinterpret_cast<double *>(W01 + ne);
+    const int v = t / kLinkSplit, part = t % kLinkSplit;
+    const bool act = v < nown;
+    const int j0 = act ? a.lk_ent_off[v0 + v] + part : 0, j1 = act ? a.lk_ent_off[v0 + v + 1] : 0;
+    uint32_t pre[kLinkAhead];
+#pragma unroll
+    for (int i = 0; i < kLinkAhead; ++i) pre[i] = j0 + i * kLinkSplit < j1 ? a.lk_ent[j0 + i * kLinkSplit] : 0u;
+    // coordinates, then edge adjoints: the first of both in flight together
+    const double r0 = a.x[0][v0], r1 = a.x[1][v0], r2 = a.x[2][v0], vb0 = a.vol[v0];
+    int e[kLinkBatch];
+    auto ids = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < kLinkBatch; ++i) e[i] = a.lk_edge[e0 + min(b + i * kLinkThreads, ne - 1)];
+    };
+    if (ne > 0) ids(t);
+    int need = 0;
+    auto row = [&](int l, double x, double y, double z, double vb) {
+        XY[l] = make_double2(x, y);
+        ZV[l] = make_double2(z, vb);
+        // differences need no wrap where every row is within a quarter period of
+        // the first; the volume part is zero where all volume adjoints are equal
+        const double far = fmax(fabs(x - r0), fmax(fabs(y - r1), fabs(z - r2)));
+        need |= (period > 0.0 && !(far <= 0.25 * period) ? 1 : 0) | (vb - vb0 == 0.0 ? 0 : 2);
+    };
+    auto node = [&](int l) { return l < nown ? v0 + l : a.lk_halo[h0 + l - nown]; };
+    const int g0 = node(min(t, rows - 1));
+    const double x0 = a.x[0][g0], y0 = a.x[1][g0], z0 = a.x[2][g0], q0 = a.vol[g0];
+    for (int b = t; b < ne; b += kLinkThreads * kLinkBatch) {
+        double w[kLinkBatch][3];
+#pragma unroll
+        for (int i = 0; i < kLinkBatch; ++i)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) w[i][d] = a.w[d][e[i]];
+        if (b == t && t < rows) row(t, x0, y0, z0, q0);
+#pragma unroll
+        for (int i = 0; i < kLinkBatch; ++i) {
+            const int j = b + i * kLinkThreads;
+            if (j < ne) {
+                W01[j] = make_double2(w[i][0], w[i][1]);
+                W2[j] = w[i][2];
+            }
+        }
+        if (b + kLinkThreads * kLinkBatch < ne) ids(b + kLinkThreads * kLinkBatch);
+    }
+    if (t >= ne && t < rows) row(t, x0, y0, z0, q0);
+    for (int l = t + kLinkThreads; l < rows; l += kLinkThreads) {
+        const int g = node(l);
+        row(l, a.x[0][g], a.x[1][g], a.x[2][g], a.vol[g]);
+    }
+    constexpr int NW = kLinkThreads / 64;
+    __shared__ int needs[NW];
+    const int any = (__any(need & 1) ? 1 : 0) | (__any(need & 2) ? 2 : 0);
+    if ((t & 63) == 0) needs[t >> 6] = any;
+    __syncthreads();
+    int all = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) all |= needs[i];
+    const bool wrap = all & 1, vol = all & 2;
+    double s[3];
+    const int vr = act ? v : 0;
+    if (vol) {
+        if (wrap) link_walk<true, true>(a, XY, ZV, W01, W2, e0, vr, j0, j1, pre, period, s);
+        else link_walk<false, true>(a, XY, ZV, W01, W2, e0, vr, j0, j1, pre, period, s);
+    } else {
+        if (wrap) link_walk<true, false>(a, XY, ZV, W01, W2, e0, vr, j0, j1, pre, period, s);
+        else link_walk<false, false>(a, XY, ZV, W01, W2, e0, vr, j0, j1, pre, period, s);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int o = 1; o < kLinkSplit; o <<= 1) s[k] += __shfl_xor(s[k], o, kLinkSplit);
+    if (act && part < 3) {
+        const double add = part == 0 ? s[0] : part == 1 ? s[1] : s[2];
+        double *xb = part == 0 ? a.xbar[0] : part == 1 ? a.xbar[1] : a.xbar[2];
+        xb[v0 + v] += add;
+    }
+}
+
 }  // namespace
 
 int launch_geometry(bool adjoint, bool gather, int T, const TetArrays &a, double period,
@@ -548,7 +715,16 @@ int launch_geometry(bool adjoint, bool gather, int T, const TetArrays &a, double
     if (T <= 0) return 0;
     if (gather) {
         const dim3 gt((T + 255) / 256), ge((a.E + 255) / 256), gn((a.N + 255) / 256);
-        if (adjoint) {
+        if (adjoint && a.lk_ent) {
+            if (a.lk_lds > 65536) {
+                const hipError_t e = hipFuncSetAttribute(
+                    reinterpret_cast<const void *>(k_link_reverse),
+                    hipFuncAttributeMaxDynamicSharedMemorySize, a.lk_lds);
+                if (e != hipSuccess) return (int)e;
+            }
+            hipLaunchKernelGGL(k_link_reverse, dim3(a.lk_chunks), dim3(kLinkThreads), a.lk_lds, st, a,
+                               period);
+        } else if (adjoint) {
             hipLaunchKernelGGL(k_interleave_w, ge, dim3(256), 0, st, a);
             hipLaunchKernelGGL(k_tet_reverse, gt, dim3(256), 0, st, T, a, period);
             hipLaunchKernelGGL(k_node_sum_xbar, gn, dim3(256), 0, st, a);

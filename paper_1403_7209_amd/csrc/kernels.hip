@@ -486,14 +486,6 @@ Arrays<T> typed(const EdgeArrays &a)
     return r;
 }
 
-// Maps workgroup k of n so that XCD (k mod 8) receives one contiguous range:
-// workgroups are dispatched round-robin over the 8 XCDs, each with its own L2.
-__device__ __forceinline__ int xcd_map(int k, int n)
-{
-    const int x = k & 7, i = k >> 3, per = n >> 3, rem = n & 7;
-    return x * per + min(x, rem) + i;
-}
-
 __device__ __forceinline__ void lds_add(double *p, double v)
 {
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

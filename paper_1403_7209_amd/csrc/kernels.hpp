@@ -20,6 +20,14 @@ enum Variant { V_COLOURED = 0, V_ATOMIC = 1, V_OWNER = 2, V_COLOURED_LDS_ATOMIC 
 
 constexpr int kOwnerThreads = 512;
 
+// Maps workgroup k of n so that XCD (k mod 8) receives one contiguous range:
+// workgroups are dispatched round-robin over the 8 XCDs, each with its own L2.
+__device__ __forceinline__ int xcd_map(int k, int n)
+{
+    const int x = k & 7, i = k >> 3, per = n >> 3, rem = n & 7;
+    return x * per + min(x, rem) + i;
+}
+
 // Lists of the fixed-order owner loop (k_edge_fixed): chunk c owns the internal
 // nodes [c K, (c+1) K) and runs its interior block, then its cut visits, in
 // rounds of kOwnerThreads visits (rounds rnd_off[c] .. rnd_off[c+1]).  In round
@@ -199,6 +207,18 @@ struct TetArrays {
     int nchunk = 0, KG = 0, L = 0;
     int RB = 0;  // ring entries of the largest batch of kGeoThreads edges of a chunk
     int DV = 0;
+    // link form of the reverse (lk_ent != nullptr): every edge's chain is a closed
+    // ring.  Chunk c holds the nodes lk_node[c] .. lk_node[c+1] - 1 as rows 0, 1,
+    // ..., then its halo nodes lk_halo[lk_halo_off[c] ..] as the rows after them;
+    // and the edges lk_edge[lk_edge_off[c] ..], slot 0, 1, ..., with the rows of
+    // their two ends (first | second << 16) in lk_ends.  Node i's entries
+    // lk_ent[lk_ent_off[i] .. lk_ent_off[i+1]) are the edges in whose ring it
+    // stands: the slot (low 12 bits) and the rows of the ring's vertices before
+    // (10 bits) and after it (10 bits).
+    const int *lk_node = nullptr, *lk_edge_off = nullptr, *lk_edge = nullptr, *lk_halo_off = nullptr,
+              *lk_halo = nullptr, *lk_ent_off = nullptr;
+    const uint32_t *lk_ends = nullptr, *lk_ent = nullptr;
+    int lk_chunks = 0, lk_lds = 0;   // LDS bytes of the largest chunk
     int write_w = 0, write_vol = 0;  // gather forward: WRITE instead of INC
     int N = 0, E = 0;
     const double *x[3] = {};
@@ -231,6 +251,16 @@ constexpr int kGeoMaxSlots = 8192;
 // LDS bytes of one ring-kernel workgroup: coordinates, then the batch's
 // entries (whole 4-byte words, one spare at each end).
 inline size_t geo_ring_lds(int L, int RB) { return (size_t)L * 24 + ((size_t)RB / 2 + 2) * 4; }
+
+// The link kernel's workgroup, its threads per node, the slots and rows an entry
+// can name, and the LDS of a chunk: 32 B per row, 24 B per slot, at most
+// kLinkLds, so that three workgroups fit a CU.
+constexpr int kLinkThreads = 512;
+constexpr int kLinkSplit = 4;
+constexpr int kLinkNodes = kLinkThreads / kLinkSplit;
+constexpr int kLinkSlots = 4096, kLinkRows = 1024;
+constexpr int kLinkLds = 52 * 1024;
+inline int link_lds(int rows, int slots) { return rows * 32 + slots * 24; }
 
 // dt[i] = cfl * vol[i] / lam[i].
 int launch_local_dt(int N, const double *vol, const double *lam, double cfl, double *dt,

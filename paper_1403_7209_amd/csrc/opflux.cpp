@@ -83,6 +83,12 @@ struct DevTetInverse {
     uint16_t *ring = nullptr, *vloc = nullptr;
     double *edge_det = nullptr;
     int nchunk = 0, KG = 0, L = 0, RB = 0, DV = 0;
+    // link form of the reverse; lk_ent == nullptr when the mesh does not fit it
+    int32_t *lk_node = nullptr, *lk_edge_off = nullptr, *lk_edge = nullptr, *lk_halo_off = nullptr,
+            *lk_halo = nullptr, *lk_ent_off = nullptr;
+    uint32_t *lk_ends = nullptr, *lk_ent = nullptr;
+    int lk_chunks = 0, lk_lds = 0;
+    bool ready = false;
 };
 
 struct opf_ctx {
@@ -732,8 +738,11 @@ int device_map(opf_ctx *ctx, opf_map m, const int32_t *&out)
 void free_tinv(opf_ctx *ctx, DevTetInverse &d)
 {
     for (int32_t *p : {d.t2n, d.t2e, d.e2t_off, d.e2t, d.n2t_off, d.n2t, d.n2t_pos, d.ring_off, d.chunk_e,
-                       d.halo_off, d.halo, d.vsec_off, d.vsec, d.vloc_off})
+                       d.halo_off, d.halo, d.vsec_off, d.vsec, d.vloc_off, d.lk_node, d.lk_edge_off,
+                       d.lk_edge, d.lk_halo_off, d.lk_halo, d.lk_ent_off})
         ctx->dfree(p);
+    ctx->dfree(d.lk_ends);
+    ctx->dfree(d.lk_ent);
     ctx->dfree(d.ring);
     ctx->dfree(d.vloc);
     ctx->dfree(d.scratch);
@@ -925,6 +934,171 @@ bool build_rings(const std::vector<int32_t> &e2n, int64_t N, int64_t E, int KG,
     return true;
 }
 
+// Host arrays of the link form (layout in opf::gpu::TetArrays).
+struct Links {
+    int nchunk = 0, lds = 0;
+    std::vector<int32_t> node, edge_off, edge, halo_off, halo, ent_off;
+    std::vector<uint32_t> ends, ent;
+};
+
+// Builds the link form from the chains of the ring form.  Returns false, and the
+// record form serves, when some edge's tets do not close a ring (a boundary:
+// the weights then depend on the edge's own ends too) or one node's edges and
+// neighbours exceed a chunk.
+bool build_links(const std::vector<int32_t> &e2n, int64_t N, int64_t E, const Rings &R, Links &K)
+{
+    using namespace opf::gpu;
+    // every (edge, ring vertex) pair by vertex, in edge order: the edge and the
+    // vertices before and after it in the ring
+    struct Item {
+        int32_t e, r, s;
+    };
+    auto chain = [&](int64_t e, std::vector<int32_t> &c) {
+        const int64_t k = std::min(e2n[2 * e], e2n[2 * e + 1]) / R.KG;
+        c.clear();
+        for (int32_t j = R.ring_off[e] + 2; j < R.ring_off[e + 1]; ++j) {
+            const int32_t l = R.ring[j];
+            c.push_back(l < R.KG ? (int32_t)(k * R.KG + l) : R.halo[R.halo_off[k] + l - R.KG]);
+        }
+    };
+    std::vector<int64_t> off(N + 1, 0);
+    std::vector<int32_t> c;
+    for (int64_t e = 0; e < E; ++e) {
+        chain(e, c);
+        if (c.size() == 1) continue;  // no tets
+        if (c.size() < 4 || c.front() != c.back()) return false;
+        for (size_t i = 1; i < c.size(); ++i) ++off[c[i] + 1];
+    }
+    for (int64_t i = 0; i < N; ++i) off[i + 1] += off[i];
+    if (off[N] >= ((int64_t)1 << 31)) return false;
+    std::vector<Item> item(off[N]);
+    {
+        std::vector<int64_t> fill(off.begin(), off.end() - 1);
+        for (int64_t e = 0; e < E; ++e) {
+            chain(e, c);
+            const size_t k = c.size() - 1;
+            for (size_t i = 0; i < k; ++i)
+                item[fill[c[i]]++] = Item{(int32_t)e, c[i == 0 ? k - 1 : i - 1], c[i + 1]};
+        }
+    }
+    // chunks: consecutive nodes until the next one would exceed the LDS, within
+    // blocks of nodes that are independent of one another
+    constexpr int64_t kBlock = 2048;
+    const int64_t nb = (N + kBlock - 1) / kBlock;
+    std::vector<Links> part(nb);
+    K.ent.resize(off[N]);
+    K.ent_off.assign(off.begin(), off.end());
+    std::vector<uint8_t> bad(nb, 0);
+    opf::parallel_run(nb, [&](int64_t b) {
+        Links &P = part[b];
+        const int64_t b0 = b * kBlock, b1 = std::min<int64_t>(N, b0 + kBlock);
+        // the block's edges and neighbours, and the chunk that last took each
+        std::vector<int32_t> es, us;
+        for (int64_t j = off[b0]; j < off[b1]; ++j) {
+            es.push_back(item[j].e);
+            us.push_back(item[j].r);
+            us.push_back(item[j].s);
+        }
+        for (int64_t v = b0; v < b1; ++v) us.push_back((int32_t)v);
+        for (std::vector<int32_t> *x : {&es, &us}) {
+            std::sort(x->begin(), x->end());
+            x->erase(std::unique(x->begin(), x->end()), x->end());
+        }
+        auto at = [](const std::vector<int32_t> &x, int32_t v) {
+            return (size_t)(std::lower_bound(x.begin(), x.end(), v) - x.begin());
+        };
+        std::vector<int32_t> etaken(es.size(), -1), utaken(us.size(), -1), eslot(es.size()), urow(us.size());
+        std::vector<int32_t> ce, cu, ne, nu;
+        auto close = [&](int64_t v0, int64_t v1) {
+            std::sort(ce.begin(), ce.end());
+            std::sort(cu.begin(), cu.end());
+            P.node.push_back((int32_t)v0);
+            int rows = (int)(v1 - v0);
+            for (int32_t u : cu) {
+                const int32_t g = us[u];
+                if (g >= v0 && g < v1) {
+                    urow[u] = (int32_t)(g - v0);
+                } else {
+                    urow[u] = rows++;
+                    P.halo.push_back(g);
+                }
+            }
+            for (size_t i = 0; i < ce.size(); ++i) {
+                eslot[ce[i]] = (int32_t)i;
+                const int64_t e = es[ce[i]];
+                P.edge.push_back((int32_t)e);
+                P.ends.push_back((uint32_t)urow[at(us, e2n[2 * e])] |
+                                 ((uint32_t)urow[at(us, e2n[2 * e + 1])] << 16));
+            }
+            P.edge_off.push_back((int32_t)P.edge.size());
+            P.halo_off.push_back((int32_t)P.halo.size());
+            P.lds = std::max(P.lds, link_lds(rows, (int)ce.size()));
+            for (int64_t j = off[v0]; j < off[v1]; ++j)
+                K.ent[j] = (uint32_t)eslot[at(es, item[j].e)] |
+                           ((uint32_t)urow[at(us, item[j].r)] << 12) |
+                           ((uint32_t)urow[at(us, item[j].s)] << 22);
+            ++P.nchunk;
+            ce.clear();
+            cu.clear();
+        };
+        int64_t v0 = b0;
+        for (int64_t v = b0; v < b1; ++v) {
+            for (int tries = 0;; ++tries) {
+                // what node v adds to the open chunk (its edges' own ends are among
+                // its neighbours too: each is the r or s of another of its entries)
+                ne.clear();
+                nu.clear();
+                auto take = [&](const std::vector<int32_t> &x, std::vector<int32_t> &taken, int32_t id,
+                                std::vector<int32_t> &news) {
+                    const size_t i = at(x, id);
+                    if (taken[i] == P.nchunk) return;
+                    taken[i] = P.nchunk;
+                    news.push_back((int32_t)i);
+                };
+                take(us, utaken, (int32_t)v, nu);
+                for (int64_t j = off[v]; j < off[v + 1]; ++j) {
+                    take(es, etaken, item[j].e, ne);
+                    take(us, utaken, item[j].r, nu);
+                    take(us, utaken, item[j].s, nu);
+                }
+                const int64_t ns = (int64_t)(ce.size() + ne.size()), nr = (int64_t)(cu.size() + nu.size());
+                if (v - v0 < kLinkNodes && ns <= kLinkSlots && nr <= kLinkRows &&
+                    link_lds((int)nr, (int)ns) <= kLinkLds) {
+                    ce.insert(ce.end(), ne.begin(), ne.end());
+                    cu.insert(cu.end(), nu.begin(), nu.end());
+                    break;
+                }
+                if (tries || v == v0) {
+                    bad[b] = 1;
+                    return;
+                }
+                for (int32_t i : ne) etaken[i] = -1;
+                for (int32_t i : nu) utaken[i] = -1;
+                close(v0, v);
+                v0 = v;
+            }
+        }
+        close(v0, b1);
+    });
+    K.edge_off.assign(1, 0);
+    K.halo_off.assign(1, 0);
+    for (int64_t b = 0; b < nb; ++b) {
+        if (bad[b]) return false;
+        const Links &P = part[b];
+        const int32_t e0 = (int32_t)K.edge.size(), h0 = (int32_t)K.halo.size();
+        K.node.insert(K.node.end(), P.node.begin(), P.node.end());
+        for (int32_t x : P.edge_off) K.edge_off.push_back(e0 + x);
+        for (int32_t x : P.halo_off) K.halo_off.push_back(h0 + x);
+        K.edge.insert(K.edge.end(), P.edge.begin(), P.edge.end());
+        K.ends.insert(K.ends.end(), P.ends.begin(), P.ends.end());
+        K.halo.insert(K.halo.end(), P.halo.begin(), P.halo.end());
+        K.nchunk += P.nchunk;
+        K.lds = std::max(K.lds, P.lds);
+    }
+    K.node.push_back((int32_t)N);
+    return true;
+}
+
 // The gather form's copies of the tet maps: tets reordered by their lowest
 // internal vertex (so that the tets around a node or an edge sit close
 // together), both maps in internal numbering, and the CSR lists of the
@@ -935,7 +1109,7 @@ int tet_inverse(opf_ctx *ctx, opf_map t2n, opf_map t2e, const opf::Plan &P, DevT
 {
     DevTetInverse &d = ctx->tinv[std::make_pair((int)t2n, (int)t2e)];
     const MapRec &mn = ctx->maps[t2n], &me = ctx->maps[t2e];
-    if (d.e2t && d.vn == mn.version && d.ve == me.version) {
+    if (d.ready && d.vn == mn.version && d.ve == me.version) {
         out = &d;
         return OPF_OK;
     }
@@ -982,25 +1156,30 @@ int tet_inverse(opf_ctx *ctx, opf_map t2n, opf_map t2e, const opf::Plan &P, DevT
         for (size_t k = 0; k < m.size(); ++k)  // ascending tet order within each list
             lst[fill[m[k]]++] = (int32_t)((k / dim) * stride + k % dim);
     };
-    std::vector<int32_t> eo, el, no, nl;
+    std::vector<int32_t> eo, el, no, nl, npos;
     invert(te, 6, 8, E, eo, el);
-    invert(tn, 4, 4, N, no, nl);
-    // the slot of every (tet, vertex) pair in its node's list: the per-tet
-    // records of the reverse are written there, so that each node sums a
-    // contiguous run
-    std::vector<int32_t> npos(4 * T);
-    for (size_t j = 0; j < nl.size(); ++j) npos[nl[j]] = (int32_t)j;
-    // bit 31 of each local edge: the edge runs from the local edge's second
-    // vertex to its first (the map orients it the other way round)
     if ((int64_t)P.e2n.size() != 2 * E) return ctx->fail(OPF_ESTATE, "the edge plan has no map");
-    for (int64_t t = 0; t < T; ++t)
-        for (int k = 0; k < 6; ++k) {
-            const int32_t e = te[6 * t + k];
-            if (P.e2n[2 * (int64_t)e] != tn[4 * t + kLocal[k][0]]) te[6 * t + k] = (int32_t)((uint32_t)e | 0x80000000u);
-        }
     const int KG = P.owner_ok ? P.cluster_size : 512;
     Rings R;
     const bool rings = build_rings(P.e2n, N, E, KG, tn, eo, el, R);
+    Links K;
+    const bool links = rings && build_links(P.e2n, N, E, R, K);
+    if (!links) {
+        invert(tn, 4, 4, N, no, nl);
+        // the slot of every (tet, vertex) pair in its node's list: the per-tet
+        // records of the reverse are written there, so that each node sums a
+        // contiguous run
+        npos.resize(4 * T);
+        for (size_t j = 0; j < nl.size(); ++j) npos[nl[j]] = (int32_t)j;
+        // bit 31 of each local edge: the edge runs from the local edge's second
+        // vertex to its first (the map orients it the other way round)
+        for (int64_t t = 0; t < T; ++t)
+            for (int k = 0; k < 6; ++k) {
+                const int32_t e = te[6 * t + k];
+                if (P.e2n[2 * (int64_t)e] != tn[4 * t + kLocal[k][0]])
+                    te[6 * t + k] = (int32_t)((uint32_t)e | 0x80000000u);
+            }
+    }
 
     free_tinv(ctx, d);
     auto up = [&](const auto &v, auto *&dst) {
@@ -1010,13 +1189,28 @@ int tet_inverse(opf_ctx *ctx, opf_map t2n, opf_map t2e, const opf::Plan &P, DevT
         hipError_t e = hipMemcpy(dst, v.data(), v.size() * sizeof(V), hipMemcpyHostToDevice);
         return e == hipSuccess ? OPF_OK : hip_fail(ctx, e, "tet incidence upload");
     };
-    int rc = up(tn, d.t2n);
-    if (!rc) rc = up(te, d.t2e);
-    if (!rc) rc = up(eo, d.e2t_off);
-    if (!rc) rc = up(el, d.e2t);
-    if (!rc) rc = up(no, d.n2t_off);
-    if (!rc) rc = up(nl, d.n2t);
-    if (!rc) rc = up(npos, d.n2t_pos);
+    // the record forms' maps and lists, where some direction needs them
+    int rc = OPF_OK;
+    if (!links) {
+        rc = up(tn, d.t2n);
+        if (!rc) rc = up(te, d.t2e);
+        if (!rc) rc = up(eo, d.e2t_off);
+        if (!rc) rc = up(el, d.e2t);
+        if (!rc) rc = up(no, d.n2t_off);
+        if (!rc) rc = up(nl, d.n2t);
+        if (!rc) rc = up(npos, d.n2t_pos);
+    } else {
+        rc = up(K.node, d.lk_node);
+        if (!rc) rc = up(K.edge_off, d.lk_edge_off);
+        if (!rc) rc = up(K.edge, d.lk_edge);
+        if (!rc) rc = up(K.ends, d.lk_ends);
+        if (!rc) rc = up(K.halo_off, d.lk_halo_off);
+        if (!rc) rc = up(K.halo.empty() ? std::vector<int32_t>(1, 0) : K.halo, d.lk_halo);
+        if (!rc) rc = up(K.ent_off, d.lk_ent_off);
+        if (!rc) rc = up(K.ent, d.lk_ent);
+        d.lk_chunks = K.nchunk;
+        d.lk_lds = K.lds;
+    }
     if (!rc && rings) {
         rc = up(R.ring_off, d.ring_off);
         if (!rc) rc = up(R.ring, d.ring);
@@ -1043,13 +1237,16 @@ int tet_inverse(opf_ctx *ctx, opf_map t2n, opf_map t2e, const opf::Plan &P, DevT
     }
     // per-tet records: the reverse's 12 values, and the forward's 19 when the
     // ring form does not serve it
-    const size_t per_tet = rings ? 12 : opf::gpu::kTetScratch;
-    d.scratch = static_cast<double *>(ctx->dalloc((size_t)T * per_tet * sizeof(double)));
-    d.wT = static_cast<double *>(ctx->dalloc((size_t)std::max<int64_t>(E, 1) * 3 * sizeof(double)));
-    if (!d.scratch || !d.wT) {
-        free_tinv(ctx, d);
-        return ctx->fail(OPF_ENOMEM, "device allocation of the tet scratch failed");
+    if (!links) {
+        const size_t per_tet = rings ? 12 : opf::gpu::kTetScratch;
+        d.scratch = static_cast<double *>(ctx->dalloc((size_t)T * per_tet * sizeof(double)));
+        d.wT = static_cast<double *>(ctx->dalloc((size_t)std::max<int64_t>(E, 1) * 3 * sizeof(double)));
+        if (!d.scratch || !d.wT) {
+            free_tinv(ctx, d);
+            return ctx->fail(OPF_ENOMEM, "device allocation of the tet scratch failed");
+        }
     }
+    d.ready = true;
     d.vn = mn.version;
     d.ve = me.version;
     out = &d;
@@ -1138,6 +1335,16 @@ int tet_loop(opf_ctx *ctx, int kernel, opf_set s, int nargs, const opf_arg *args
             ta.KG = inv->KG;
             ta.L = inv->L;
             ta.RB = inv->RB;
+            ta.lk_node = inv->lk_node;
+            ta.lk_edge_off = inv->lk_edge_off;
+            ta.lk_edge = inv->lk_edge;
+            ta.lk_ends = inv->lk_ends;
+            ta.lk_halo_off = inv->lk_halo_off;
+            ta.lk_halo = inv->lk_halo;
+            ta.lk_ent_off = inv->lk_ent_off;
+            ta.lk_ent = inv->lk_ent;
+            ta.lk_chunks = inv->lk_chunks;
+            ta.lk_lds = inv->lk_lds;
         }
     } else {
         rc = device_map(ctx, t2n, ta.t2n);

@@ -907,6 +907,8 @@ int build_plan(int64_t N, int64_t E, const int32_t *e2n_user, const PlanOptions 
     return OPF_OK;
 }
 
+void parallel_run(int64_t n, const std::function<void(int64_t)> &f) { parallel_for(n, f); }
+
 void build_fixed(const Plan &P, int K, int NT, FixedLists &F)
 {
     F = FixedLists();

@@ -9,6 +9,7 @@
 #pragma once
 
 #include <cstdint>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -132,6 +133,9 @@ struct FixedLists {
 // Builds the lists over the plan's owner clusters (K = cluster_size), or, for
 // K < cluster_size, over chunks of K nodes with visits of their own.
 void build_fixed(const Plan &plan, int K, int NT, FixedLists &out);
+
+// Runs f(0) .. f(n - 1) on a few host threads.
+void parallel_run(int64_t n, const std::function<void(int64_t)> &f);
 
 struct VerifyResult {
     bool ok = true;
