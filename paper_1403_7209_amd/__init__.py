@@ -665,11 +665,11 @@ class FluxProblem:
         gives the weight sensitivities, the geometry reverse carries them to the
         node coordinates.  Returns xbar (3, N), internal numbering."""
         dev = self.ctx.torch_device
-        qbar = torch.zeros((6, self.N), dtype=torch.float64, device=dev)
+        qbar, access = _increments((6, self.N), dev, variant)
         nbar = torch.empty((3, self.E), dtype=torch.float64, device=dev)
         self.ctx.edge_flux_adjoint(self.edges, self.e2n, self.dat(self.qa, "q"), self.w,
                                    self.dat(rbar_t, "rbar"), self.dat(qbar, "qbar"),
-                                   self.dat(nbar, "nbar", edges=True), self.gamma, variant, INC,
+                                   self.dat(nbar, "nbar", edges=True), self.gamma, variant, access,
                                    stream)
         xbar = torch.zeros((3, self.N), dtype=torch.float64, device=dev)
         volbar = torch.zeros(self.N, dtype=torch.float64, device=dev)
@@ -725,6 +725,14 @@ class FluxProblem:
         return np.sqrt(self.ss.cpu().numpy() / self.N)
 
 
+def _increments(shape, device, variant):
+    """A new node array for an edge loop's sums and the access to give it: the OWNER
+    variant writes each total once, so it needs no zeros and reads nothing back."""
+    if variant == OWNER:
+        return torch.empty(shape, dtype=torch.float64, device=device), WRITE
+    return torch.zeros(shape, dtype=torch.float64, device=device), INC
+
+
 class EdgeFluxFunction(torch.autograd.Function):
     """res = R(q, n) on a FluxProblem (internal numbering, FP64).  The backward
     pass runs the hand-written adjoint edge kernel, which recomputes the edge
@@ -732,10 +740,10 @@ class EdgeFluxFunction(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, problem, q, w, variant=COLOURED):
-        res = torch.zeros((6, problem.N), dtype=torch.float64, device=q.device)
+        res, access = _increments((6, problem.N), q.device, variant)
         problem.ctx.edge_flux(problem.edges, problem.e2n, problem.dat(q.detach(), "q"),
                               problem.dat(w.detach(), "n", edges=True), problem.dat(res, "res"),
-                              problem.gamma, variant)
+                              problem.gamma, variant, access)
         ctx.problem, ctx.variant = problem, variant
         ctx.save_for_backward(q, w)
         return res
@@ -745,10 +753,10 @@ class EdgeFluxFunction(torch.autograd.Function):
         q, w = ctx.saved_tensors
         p = ctx.problem
         rbar = rbar.contiguous()
-        qbar = torch.zeros_like(q)
+        qbar, access = _increments(q.shape, q.device, ctx.variant)
         nbar = torch.empty_like(w)
         p.ctx.edge_flux_adjoint(p.edges, p.e2n, p.dat(q.detach(), "q"),
                                 p.dat(w.detach(), "n", edges=True), p.dat(rbar, "rbar"),
                                 p.dat(qbar, "qbar"), p.dat(nbar, "nbar", edges=True), p.gamma,
-                                ctx.variant)
+                                ctx.variant, access)
         return None, qbar, nbar, None
