@@ -75,7 +75,8 @@ static __device__ __align__(256) double scratch[opf::gpu::kSumTail + 6 * opf::gp
 #define OPF_FLUX2_CUT_BATCH 1
 #endif
 // The second-order loop holds 30 values per node in LDS: one workgroup per CU,
-// so its workgroups take more threads (768: it spills registers at 1024).  The
+// so its workgroups take more threads (1024 with one edge each: 2.1M nodes 373
+// us, 768 with two: 382, 512 with one: 400).  The
 // gradient runs in halves of 12 values per node, three 512-thread workgroups
 // per CU.
 #ifndef OPF_GRAD_BATCH
@@ -85,10 +86,10 @@ static __device__ __align__(256) double scratch[opf::gpu::kSumTail + 6 * opf::gp
 #define OPF_GRAD_THREADS 512
 #endif
 #ifndef OPF_FLUX2_BATCH
-#define OPF_FLUX2_BATCH 2
+#define OPF_FLUX2_BATCH 1
 #endif
 #ifndef OPF_FLUX2_THREADS
-#define OPF_FLUX2_THREADS 768
+#define OPF_FLUX2_THREADS 1024
 #endif
 
 namespace opf {
@@ -803,18 +804,19 @@ __device__ __forceinline__ void block_sum(double (&acc)[NV], double *out)
     }
 }
 
-// out[0..5] = the sums over the workgroup's NT threads of acc[0..5], through
-// LDS (buf: 6 * NT doubles, free for this use) in a fixed tree: 64 lanes x 8,
-// then 8, then the last 8.  Three LDS rounds instead of the 36 dependent
-// cross-lane shuffles of a wavefront reduction of six doubles.
-template <int NT>
+// out[0..5] = the sums over the workgroup's first 512 threads of acc[0..5],
+// through LDS (buf: 6 * 512 doubles, free for this use) in a fixed tree: 64
+// lanes x 8, then 8, then the last 8.  Three LDS rounds instead of the 36
+// dependent cross-lane shuffles of a wavefront reduction of six doubles.
 __device__ __forceinline__ void lds_sum6(const double (&acc)[6], double *buf, double *out)
 {
-    static_assert(NT == 512, "the tree is laid out for 512 threads");
+    constexpr int NT = 512;
     const int t = threadIdx.x;
     __syncthreads();  // buf may still be read
+    if (t < NT) {
 #pragma unroll
-    for (int k = 0; k < 6; ++k) buf[k * NT + t] = acc[k];
+        for (int k = 0; k < 6; ++k) buf[k * NT + t] = acc[k];
+    }
     __syncthreads();
     if (t < 6 * 64) {
         const int k = t >> 6, j = t & 63;
@@ -874,6 +876,15 @@ struct StagePtrs {
     double *res[6];    // fixed-order loop: added to the totals and cleared, or null
 };
 
+// Waves per SIMD the registers must allow: a workgroup of 1024 threads has a CU
+// to itself.
+template <typename T, class Op, int NT>
+constexpr int owner_waves()
+{
+    if (NT == 1024) return 4;
+    return OwnerTune<T, Op>::WAVES > 0 ? OwnerTune<T, Op>::WAVES : 1;
+}
+
 // HALVES: two workgroups per cluster, b and b + 8 of each 16 (dispatched to the
 // same XCD, so that the second reads the cluster's edges from L2), each
 // running Op on its half of the node inputs and outputs (grid: 16 per 8
@@ -881,7 +892,7 @@ struct StagePtrs {
 // (where the op takes them).
 template <typename T, class Op, int NT, int KC, bool STAGE = false, bool HALVES = false,
           bool HINT = false>
-__global__ __launch_bounds__(NT, (OwnerTune<T, Op>::WAVES > 0 ? OwnerTune<T, Op>::WAVES : 1)) void k_edge_owner(
+__global__ __launch_bounds__(NT, (owner_waves<T, Op, NT>())) void k_edge_owner(
     OwnerPtrs p, Arrays<T> a0, T gamma, int N, int Kr, int ncl, int remap, int overwrite,
     StagePtrs<T> sp = {})
 {
@@ -969,17 +980,27 @@ __global__ __launch_bounds__(NT, (OwnerTune<T, Op>::WAVES > 0 ? OwnerTune<T, Op>
     // (2) cut visits
     constexpr int BC = OwnerTune<T, Op>::BC;
     const int s0 = p.cv_off[c], ns = p.cv_off[c + 1] - s0;
+    int eidn[BC], othn[BC], ownn[BC];  // the next round's visits
+    auto visits = [&](int k0) {
+#pragma unroll
+        for (int b = 0; b < BC; ++b) {
+            const int k = k0 + b * NT;
+            eidn[b] = -1;
+            if (k < ns) {
+                eidn[b] = ld1<S>(p.cv_eid, s0 + k);
+                othn[b] = ld1<S>(p.cv_oth, s0 + k);
+                ownn[b] = (int)ld1<S>(p.cv_own, s0 + k);
+            }
+        }
+    };
+    visits(threadIdx.x);
     for (int k0 = threadIdx.x; k0 < ns; k0 += NT * BC) {
         int eid[BC], oth[BC], own[BC];
 #pragma unroll
         for (int b = 0; b < BC; ++b) {
-            const int k = k0 + b * NT;
-            eid[b] = -1;
-            if (k < ns) {
-                eid[b] = ld1<S>(p.cv_eid, s0 + k);
-                oth[b] = ld1<S>(p.cv_oth, s0 + k);
-                own[b] = (int)ld1<S>(p.cv_own, s0 + k);
-            }
+            eid[b] = eidn[b];
+            oth[b] = othn[b];
+            own[b] = ownn[b];
         }
         T w[BC][Op::NW], xf[BC][Op::NIN];
 #pragma unroll
@@ -991,6 +1012,7 @@ __global__ __launch_bounds__(NT, (OwnerTune<T, Op>::WAVES > 0 ? OwnerTune<T, Op>
 #pragma unroll
             for (int v = 0; v < Op::NIN; ++v) xf[b][v] = ld(a.x[v], g);
         }
+        visits(k0 + NT * BC);
 #pragma unroll
         for (int b = 0; b < BC; ++b) {
             if (eid[b] < 0) continue;
@@ -1043,9 +1065,9 @@ __global__ __launch_bounds__(NT, (OwnerTune<T, Op>::WAVES > 0 ? OwnerTune<T, Op>
             }
         }
         bool done = false;
-        if constexpr (NT == 512) {
-            if (K >= NT) {  // the accumulators hold 6 * NT doubles
-                lds_sum6<NT>(acc, sy, sp.partial + 6 * c);
+        if constexpr (NT == 512 || KC == 512) {  // one node per thread, the first 512
+            if (K >= 512) {  // the accumulators hold 6 * 512 doubles
+                lds_sum6(acc, sy, sp.partial + 6 * c);
                 done = true;
             }
         }
@@ -1261,7 +1283,7 @@ __global__ __launch_bounds__(kOwnerThreads, (FixedTune<T, Op>::WAVES)) void k_ed
         }
         double *out = sp.partial + 6 * c;
         if constexpr (P == 1) {
-            lds_sum6<NT>(sq, Y, out);
+            lds_sum6(sq, Y, out);
         } else {
             static_assert(NV == 1 && KC <= 64, "a sum's nodes are lanes of one wavefront");
 #pragma unroll
@@ -1328,9 +1350,9 @@ __global__ __launch_bounds__(kRkThreads) void k_local_dt(int N, const double *__
 constexpr int kSumThreads = 256;
 
 __global__ __launch_bounds__(kSumThreads) void k_sum_partials(int nparts, double *buf0, double *ss0,
-                                                             int overwrite)
+                                                             int64_t stride, int overwrite)
 {
-    double *buf = buf0 + (size_t)blockIdx.y * (kSumTail + 6 * (size_t)nparts);
+    double *buf = buf0 + blockIdx.y * stride;
     double *ss = ss0 + 6 * blockIdx.y;
     const int groups = (int)gridDim.x;
     const double *rows = buf + kSumTail;
@@ -1545,6 +1567,18 @@ bool owner_streams(const DevPlan &P, bool stage)
     return bytes > kMallBytes;
 }
 
+// Workgroups of 1024 threads where the launch has at most one for each of the
+// 256 CUs: a workgroup's chain of rounds then sets the time, and twice the
+// threads halve it (five fused stages, 110,592 nodes: FP64 77 -> 73 us, FP32 64
+// -> 55; with more workgroups than CUs they no longer share one: 262,144 nodes,
+// FP64 113 -> 129 us).
+constexpr int kOwnerWide = 1024, kOwnerWideGrid = 256;
+template <typename T, class O>
+constexpr bool owner_wide()
+{
+    return OwnerTune<T, O>::NT != kOwnerWide;
+}
+
 // Launches the owner kernel of op O (KC: compile-time cluster size or 0).
 template <typename T, class O, int NT, int KC, bool STAGE, bool H>
 void launch_owner_kc(bool hint, int grid, size_t lds, hipStream_t st, const OwnerPtrs &op,
@@ -1567,6 +1601,13 @@ void launch_owner(bool hint, int grid, size_t lds, hipStream_t st, const OwnerPt
                   const Arrays<T> &a, T gamma, const DevPlan &P, const LaunchOpts &lo,
                   int overwrite, const StagePtrs<T> &sp)
 {
+    if constexpr (owner_wide<T, O>()) {
+        if (P.K == kOwnerKC && grid <= kOwnerWideGrid) {
+            launch_owner_kc<T, O, kOwnerWide, kOwnerKC, STAGE, H>(false, grid, lds, st, op, a, gamma, P,
+                                                                  lo, overwrite, sp);
+            return;
+        }
+    }
     if (P.K == kOwnerKC)
         launch_owner_kc<T, O, NT, kOwnerKC, STAGE, H>(hint, grid, lds, st, op, a, gamma, P, lo,
                                                       overwrite, sp);
@@ -1706,6 +1747,12 @@ int raise_owner(size_t bytes)
     if (!rc)
         rc = raise_one(reinterpret_cast<const void *>(&k_edge_owner<T, O, NT, kOwnerKC, STAGE, H, false>),
                        bytes);
+    if constexpr (owner_wide<T, O>()) {
+        if (!rc)
+            rc = raise_one(
+                reinterpret_cast<const void *>(&k_edge_owner<T, O, kOwnerWide, kOwnerKC, STAGE, H, false>),
+                bytes);
+    }
     if constexpr (OwnerTune<T, O>::STREAM) {
         if (!rc)
             rc = raise_one(reinterpret_cast<const void *>(&k_edge_owner<T, O, NT, 0, STAGE, H, true>),
@@ -1830,11 +1877,12 @@ int launch_edge_stage(bool fp32, const DevPlan &P, const EdgeArrays &a, const No
                 : run_stage<double>(P, a, na, gamma, adt, rows, st, lo);
 }
 
-int launch_sum_partials(int nrows, int nsets, double *buf, double *ss, bool overwrite, hipStream_t st)
+int launch_sum_partials(int nrows, int nsets, double *buf, int64_t stride, double *ss, bool overwrite,
+                        hipStream_t st)
 {
     const int groups = nrows <= kSumAlone ? 1 : kSumGroups;
     hipLaunchKernelGGL(k_sum_partials, dim3(groups, nsets), dim3(kSumThreads), 0, st, nrows, buf, ss,
-                       overwrite ? 1 : 0);
+                       stride, overwrite ? 1 : 0);
     return (int)hipGetLastError();
 }
 
@@ -1863,7 +1911,7 @@ static int run_rk(int N, const NodeArrays &a, double alpha_dt, double *ss, doubl
     hipLaunchKernelGGL((k_rk_stage<T>), dim3(grid), dim3(kRkThreads), 0, st, N, p, alpha_dt,
                        partial + kSumTail, keep_res ? 1 : 0);
     const int e = (int)hipGetLastError();
-    return e ? e : launch_sum_partials(grid, 1, partial, ss, false, st);
+    return e ? e : launch_sum_partials(grid, 1, partial, 0, ss, false, st);
 }
 
 int launch_rk_stage(bool fp32, int N, const NodeArrays &a, double alpha_dt, double *ss,

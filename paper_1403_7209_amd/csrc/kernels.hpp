@@ -47,9 +47,11 @@ struct FixedPlan {
 };
 // The largest chunk of the fixed-order loop: one node per thread.
 constexpr int kFixedMaxK = kOwnerThreads;
-// The chunk of a small mesh, and the most nodes of one (see fixed_chunk).
+// The chunk of a small mesh, the most nodes of one (see fixed_chunk), and the
+// most for which the owner variant takes it (see takes_fixed).
 constexpr int kFixedFine = 32;
 constexpr int kFixedFineNodes = 65536;
+constexpr int kFixedFineOwner = 24576;
 // Stages of one iteration.
 constexpr int kStages = 5;
 
@@ -85,9 +87,11 @@ struct DevPlan {
     const uint16_t *cvf_own = nullptr;
     FixedPlan fixed;
     // flat colouring: colour c runs edges flat_eid[flat_off[c] .. flat_off[c+1])
-    // partial sums of the fused stages: per stage of an iteration kSumTail + 6
-    // doubles per cluster or chunk
+    // partial sums of the fused stages: stage_stride doubles per stage of an
+    // iteration, kSumTail and 6 per cluster or chunk (whichever are more, so that
+    // the counters keep their places)
     double *stage_partial = nullptr;
+    int64_t stage_stride = 0;
     int nflat = 0;
     std::vector<int64_t> flat_off;  // host copy [nflat+1]
     const int *flat_eid = nullptr;  // [E]
@@ -147,10 +151,9 @@ int launch_edge_stage(bool fp32, const DevPlan &P, const EdgeArrays &a, const No
                       double gamma, double adt, double *rows, hipStream_t stream,
                       const LaunchOpts &lo);
 
-// The second pass over `nsets` buffers of partial sums (kSumTail + 6 nrows
-// doubles each, one after the other): ss[6 k + v] += the sums of set k, or = with
-// overwrite.
-int launch_sum_partials(int nrows, int nsets, double *buf, double *ss, bool overwrite,
+// The second pass over `nsets` buffers of partial sums, `stride` doubles apart
+// (even): ss[6 k + v] += the sums of set k, or = with overwrite.
+int launch_sum_partials(int nrows, int nsets, double *buf, int64_t stride, double *ss, bool overwrite,
                         hipStream_t stream);
 
 // Clusters whose partial sums fit the library's static device scratch (the

@@ -311,7 +311,8 @@ int upload_plan(opf_ctx *ctx, PlanRec &pr)
         if (!rc) rc = upload_fixed(ctx, pr);
         if (!rc) {
             const size_t rows = (size_t)std::max(D.ncl, D.fixed.nchunk);
-            const size_t nb = sizeof(double) * opf::gpu::kStages * (opf::gpu::kSumTail + 6 * rows);
+            D.stage_stride = (int64_t)(opf::gpu::kSumTail + 6 * rows);
+            const size_t nb = sizeof(double) * opf::gpu::kStages * (size_t)D.stage_stride;
             D.stage_partial = static_cast<double *>(ctx->dalloc(nb));
             if (!D.stage_partial) {
                 rc = ctx->fail(OPF_ENOMEM, "device allocation of plan arrays failed");
@@ -522,13 +523,16 @@ int check_gbl_disjoint(opf_ctx *ctx, const void *p, size_t bytes, std::initializ
 
 // Whether a loop of this variant runs over the plan's fixed-order lists: the
 // coloured variant wherever there are any (the same fixed order on every run,
-// without a launch per partition colour); the owner variant on a small mesh,
-// whose clusters would leave most CUs idle.
+// without a launch per partition colour); the owner variant up to 24,576 nodes,
+// where its few clusters take as long as one of them does: flux and adjoint at
+// 8,000 nodes 6.3 and 8.5 us against 11.2 and 14.4 over the clusters, at 21,952
+// 9.9 and 16.6 against 11.7 and 15.4, at 46,656 17.0 and 27.4 against 12.2 and
+// 16.4.
 bool takes_fixed(const PlanRec &pr, int variant)
 {
     const opf::gpu::FixedPlan &X = pr.dev.fixed;
     if (variant == OPF_V_COLOURED) return X.K > 0;
-    return variant == OPF_V_OWNER && X.fine;
+    return variant == OPF_V_OWNER && X.fine && pr.dev.N <= opf::gpu::kFixedFineOwner;
 }
 
 int edge_loop(opf_ctx *ctx, int kernel, opf_set s, int nargs, const opf_arg *args, int ngbl,
@@ -2013,18 +2017,18 @@ int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat
     if (how.res >= 0)
         for (int c = 0; c < 6; ++c) na.res[c] = (double *)comp(ctx->dats[how.res], c);
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    const int rows = stage_rows(pr, how.variant);
     if (how.set >= 0) {
-        partial += (size_t)how.set * (opf::gpu::kSumTail + 6 * (size_t)rows);
+        partial += how.set * pr.dev.stage_stride;
         const int e = opf::gpu::launch_edge_stage(fp32, pr.dev, ea, na, gamma, alpha,
                                                   partial + opf::gpu::kSumTail, st, lo);
         return e ? hip_fail(ctx, (hipError_t)e, "fused loop launch") : OPF_OK;
     }
+    const int rows = stage_rows(pr, how.variant);
     if (!noalloc) rc = scratch_begin(ctx, st);
     if (rc) return rc;
     int e = opf::gpu::launch_edge_stage(fp32, pr.dev, ea, na, gamma, alpha,
                                         partial + opf::gpu::kSumTail, st, lo);
-    if (!e) e = opf::gpu::launch_sum_partials(rows, 1, partial, ss_dev, false, st);
+    if (!e) e = opf::gpu::launch_sum_partials(rows, 1, partial, 0, ss_dev, false, st);
     if (e) return hip_fail(ctx, (hipError_t)e, "fused loop launch");
     return noalloc ? OPF_OK : scratch_end(ctx, st);
 }
@@ -2091,7 +2095,7 @@ int opf_rk_iteration(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_da
     if (!rc) {
         const PlanRec &pr = *it->second;
         const int e = opf::gpu::launch_sum_partials(stage_rows(pr, variant), S, pr.dev.stage_partial,
-                                                    ss_dev, true, st);
+                                                    pr.dev.stage_stride, ss_dev, true, st);
         if (e) rc = hip_fail(ctx, (hipError_t)e, "iteration launch");
     }
     const std::string why = ctx->err;

@@ -1,9 +1,9 @@
 """The fixed-order edge loop (coloured variant, and every loop of a small mesh's
 owner variant) against the oracle, at the edges of its chunks and rounds:
 meshes of fewer nodes than a chunk, of one chunk more, with a last chunk of one
-node, at both sides of the small-mesh limit (65,536 nodes), cluster sizes with
-and without a compile-time instance, and a node with more edges than a round
-has visits.  Results must be the same bits on every run."""
+node, at both sides of the small-mesh limits (24,576 nodes for the owner variant,
+65,536 for the coloured one), cluster sizes with and without a compile-time
+instance, and a node with more edges than a round has visits.  Results must be the same bits on every run."""
 import numpy as np
 import pytest
 import torch
@@ -57,7 +57,8 @@ CASES = {  # graph, cluster size, variants
     "fine-513": (lambda: chain(513), 512, (pk.COLOURED, pk.OWNER)),
     "fine-33-of-64": (lambda: chain(65), 64, (pk.COLOURED, pk.OWNER)),
     "fine-box11": (lambda: box(11), 512, (pk.COLOURED, pk.OWNER)),
-    "fine-limit": (lambda: chain(65536), 512, (pk.COLOURED, pk.OWNER)),
+    "owner-limit": (lambda: chain(24576), 512, (pk.COLOURED, pk.OWNER)),
+    "fine-limit": (lambda: chain(65536), 512, (pk.COLOURED,)),
     "above-limit": (lambda: chain(65537), 512, (pk.COLOURED,)),
     "run-time-chunk": (lambda: chain(65537), 200, (pk.COLOURED,)),
     "box41-of-64": (lambda: box(41), 64, (pk.COLOURED,)),
@@ -119,6 +120,42 @@ def test_loops_and_iteration(name):
             p.residual(p.qa, r, v, res_access=pk.WRITE)
             ctx.sync()
             assert close(p, r, res)
+
+
+@pytest.mark.parametrize("N", [24577, 65536, 131072, 131073])
+def test_owner_workgroup_widths(N):
+    """The owner variant above the small-mesh limit and on both sides of one
+    workgroup per CU (256 clusters; 128 for the gradient's two halves)."""
+    g = chain(N)
+    print(f"[owner widths: {g.N} nodes]", flush=True)
+    ctx = pk.Context(DEV)
+    f64 = dict(dtype=torch.float64, device=DEV)
+    res, G = oracle.residual(g.e2n, g.q, g.w), oracle.gradient(g.e2n, g.q, g.w)
+    rbar = np.random.default_rng(3).normal(size=(6, g.N))
+    qb, nb = oracle.adjoint(g.e2n, g.q, g.w, rbar)
+    dt = oracle.dt(g.e2n, g.q, g.w, g.vol)
+    q1, ss1 = oracle.rk_iteration(g.e2n, g.q, g.w, g.vol, dt)
+    p = pk.FluxProblem(ctx, g.e2n, g.w, g.vol, g.q)
+    p.set_edge_vectors(g.dx)
+    r, gr, r2 = torch.empty(6, g.N, **f64), torch.empty(18, g.N, **f64), torch.empty(6, g.N, **f64)
+    q, n = torch.zeros(6, g.N, **f64), torch.zeros(3, len(g.e2n), **f64)
+    p.residual(p.qa, r, pk.OWNER, res_access=pk.WRITE)
+    p.gradient(p.qa, gr, pk.OWNER, pk.WRITE)
+    p.residual2(p.qa, p.nodes_in(G), r2, pk.OWNER, pk.WRITE)
+    ctx.edge_flux_adjoint(p.edges, p.e2n, p.dat(p.qa), p.w, p.dat(p.nodes_in(rbar)), p.dat(q),
+                          p.dat(n, edges=True), p.gamma, pk.OWNER)
+    ctx.sync()
+    assert close(p, r, res) and close(p, gr, G) and close(p, q, qb) and close(p, n, nb, edges=True)
+    assert close(p, r2, oracle.residual2(g.e2n, g.q, G, g.vol, g.w, g.dx))
+    assert abs(p.compute_dt(0.5, pk.OWNER) - dt) <= 1e-12 * dt
+    p.rk_iteration(dt, pk.OWNER)
+    ctx.sync()
+    assert close(p, p.qa, q1) and normwise(p.ss.cpu().numpy().T, ss1.T) <= TOL
+    # the coloured iteration's partial sums share the buffer with other rows
+    p.qa.copy_(p.nodes_in(g.q))
+    p.rk_iteration(dt)
+    ctx.sync()
+    assert close(p, p.qa, q1) and normwise(p.ss.cpu().numpy().T, ss1.T) <= TOL
 
 
 def test_coloured_iteration_takes_up_the_residual():
