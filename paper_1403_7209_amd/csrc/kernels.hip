@@ -390,42 +390,54 @@ struct OpFlux2 {
 
 // B: edges each thread resolves before computing in the interior loop, BC in
 // the cut-visit loop (whose gathered records cost registers).
-// FOREIGN: the cut visits in the plan's foreign-node order (the lanes of a
-// wavefront share foreign records: pays where those records are wide and
-// bandwidth binds) rather than the bank-spread order (pays where the LDS
-// updates bind).
+// ORDER: the plan's order of the cut visits.  FOREIGN (by foreign node): the
+// lanes of a wavefront share foreign records, which pays where those are wide
+// (second order, 25 values: 373 us against 392 in edge order at 2.1M nodes; the
+// adjoint's 12 values take the same time in both).  EDGE: the edge inputs are
+// read coalesced (a wavefront's 64 weights lie in 5 cache lines instead of 14),
+// which pays for the FP64 flux (five stages of 4.1M, 1M and 185,000 nodes: 1-9 %
+// less than in foreign order) and the fixed-order loops (3 %).  SPREAD (the owned
+// ends of 16 visits in distinct LDS banks): the FP32 flux and the gradient, bound
+// by their LDS updates (edge order costs the FP32 flux 2 %).
 // STREAM: non-temporal hints on the loop's once-touched data (ld1/st1) when
 // its arrays exceed the last-level cache (owner_streams).  They pay in the
 // flux loops (3-5 %) and cost in the adjoint, gradient and second-order loops
 // (4-17 %), whose wider records or scattered edge writes do better through
 // the normal cache policy.
+enum CutOrder { SPREAD, FOREIGN, EDGE };
+
 template <typename T, class Op>
 struct OwnerTune {
     static constexpr int B = 2, BC = 2, WAVES = 0, NT = kOwnerThreads;
-    static constexpr bool FOREIGN = false, STREAM = false;
+    static constexpr CutOrder ORDER = SPREAD;
+    static constexpr bool STREAM = false;
 };
 template <>
 struct OwnerTune<float, OpFlux> {
     static constexpr int B = OPF_FLUX32_BATCH, BC = OPF_FLUX32_CUT_BATCH, WAVES = OPF_FLUX32_WAVES,
                          NT = kOwnerThreads;
-    static constexpr bool FOREIGN = false, STREAM = true;
+    static constexpr CutOrder ORDER = SPREAD;
+    static constexpr bool STREAM = true;
 };
 template <>
 struct OwnerTune<double, OpFlux> {
     static constexpr int B = OPF_FLUX64_BATCH, BC = OPF_FLUX64_CUT_BATCH, WAVES = OPF_FLUX64_WAVES,
                          NT = kOwnerThreads;
-    static constexpr bool FOREIGN = true, STREAM = true;
+    static constexpr CutOrder ORDER = EDGE;
+    static constexpr bool STREAM = true;
 };
 template <>
 struct OwnerTune<double, OpAdjoint> {
     static constexpr int B = OPF_ADJ_BATCH, BC = OPF_ADJ_CUT_BATCH, WAVES = OPF_ADJ_WAVES,
                          NT = kOwnerThreads;
-    static constexpr bool FOREIGN = true, STREAM = false;
+    static constexpr CutOrder ORDER = FOREIGN;
+    static constexpr bool STREAM = false;
 };
 template <>
 struct OwnerTune<double, OpGradH> {
     static constexpr int B = OPF_GRAD_BATCH, BC = OPF_GRAD_BATCH, WAVES = 0, NT = OPF_GRAD_THREADS;
-    static constexpr bool FOREIGN = false, STREAM = false;
+    static constexpr CutOrder ORDER = SPREAD;
+    static constexpr bool STREAM = false;
 };
 
 // The op the owner variant runs for Op, and whether in two halves per cluster.
@@ -443,7 +455,8 @@ template <>
 struct OwnerTune<double, OpFlux2> {
     static constexpr int B = OPF_FLUX2_BATCH, BC = OPF_FLUX2_CUT_BATCH, WAVES = 0,
                          NT = OPF_FLUX2_THREADS;
-    static constexpr bool FOREIGN = true, STREAM = false;
+    static constexpr CutOrder ORDER = FOREIGN;
+    static constexpr bool STREAM = false;
 };
 
 // ----------------------------------------------------------- plumbing -- */
@@ -1538,9 +1551,10 @@ constexpr size_t owner_dyn_lds(int K)
     return stage_bytes<T, Op>(K) + (size_t)Op::NOUT * owner_acc_rows(K) * sizeof(double);
 }
 
-OwnerPtrs owner_ptrs(const DevPlan &P, bool foreign)
+OwnerPtrs owner_ptrs(const DevPlan &P, CutOrder order)
 {
-    if (foreign) return OwnerPtrs{P.iblk, P.iw, P.cv_off, P.cvf_eid, P.cvf_oth, P.cvf_own};
+    if (order == FOREIGN) return OwnerPtrs{P.iblk, P.iw, P.cv_off, P.cvf_eid, P.cvf_oth, P.cvf_own};
+    if (order == EDGE) return OwnerPtrs{P.iblk, P.iw, P.cv_off, P.cve_eid, P.cve_oth, P.cve_own};
     return OwnerPtrs{P.iblk, P.iw, P.cv_off, P.cv_eid, P.cv_oth, P.cv_own};
 }
 
@@ -1624,7 +1638,7 @@ int run_owner(const DevPlan &P, const EdgeArrays &a, double gamma, hipStream_t s
     using O = typename OwnerOp<Op>::type;
     constexpr bool H = OwnerOp<Op>::HALVES;
     const size_t lds = owner_dyn_lds<T, O>(P.K);
-    const OwnerPtrs op = owner_ptrs(P, OwnerTune<T, O>::FOREIGN);
+    const OwnerPtrs op = owner_ptrs(P, OwnerTune<T, O>::ORDER);
     constexpr int NT = OwnerTune<T, O>::NT;
     const int grid = H ? 16 * ((P.ncl + 7) / 8) : P.ncl;
     launch_owner<T, O, NT, false, H>(owner_streams<T, O>(P, false), grid, lds, st, op, typed<T>(a),
@@ -1654,7 +1668,7 @@ int run_owner_stage(const DevPlan &P, const EdgeArrays &a, const StagePtrs<T> &s
 {
     if (!P.owner_ok || P.ncl <= 0) return (int)hipErrorInvalidValue;
     const size_t lds = owner_dyn_lds<T, OpFlux>(P.K);
-    const OwnerPtrs op = owner_ptrs(P, OwnerTune<T, OpFlux>::FOREIGN);
+    const OwnerPtrs op = owner_ptrs(P, OwnerTune<T, OpFlux>::ORDER);
     launch_owner<T, OpFlux, kOwnerThreads, true, false>(owner_streams<T, OpFlux>(P, true), P.ncl,
                                                         lds, st, op, typed<T>(a), (T)gamma, P, lo,
                                                         0, sp);

@@ -82,7 +82,10 @@ struct DevPlan {
     const int *cv_oth = nullptr;     // its other end (internal node), bit 31 set when
                                      // the owned end is the edge's second node
     const uint16_t *cv_own = nullptr; // offset of the owned end in the cluster
-    // the same visits ordered by foreign node within each run (same offsets)
+    // the same visits ordered by foreign node, and by edge, within each run (same
+    // offsets)
+    const int *cve_eid = nullptr, *cve_oth = nullptr;
+    const uint16_t *cve_own = nullptr;
     const int *cvf_eid = nullptr, *cvf_oth = nullptr;
     const uint16_t *cvf_own = nullptr;
     FixedPlan fixed;

@@ -204,10 +204,10 @@ int upload_owner(opf_ctx *ctx, PlanRec &pr)
     int rc = upload(ctx, pr, iblk, D.iblk);
     if (!rc) rc = upload(ctx, pr, iw, D.iw);
     if (!rc) rc = upload(ctx, pr, cv_off, D.cv_off);
-    // both orders of the cut visits: edge, other end | orientation, owned offset
-    for (int order = 0; order < 2 && !rc; ++order) {
-        const std::vector<int32_t> &ce = order ? P.cl_cutf_eid : P.cl_cut_eid;
-        const std::vector<uint8_t> &ch = order ? P.cl_cutf_end : P.cl_cut_end;
+    // every order of the cut visits: edge, other end | orientation, owned offset
+    for (int order = 0; order < 3 && !rc; ++order) {
+        const std::vector<int32_t> &ce = order == 2 ? P.cl_cute_eid : order ? P.cl_cutf_eid : P.cl_cut_eid;
+        const std::vector<uint8_t> &ch = order == 2 ? P.cl_cute_end : order ? P.cl_cutf_end : P.cl_cut_end;
         std::vector<int> cv_oth(nv);
         std::vector<uint16_t> cv_own(nv);
         for (int64_t c = 0; c < ncl; ++c)
@@ -217,9 +217,9 @@ int upload_owner(opf_ctx *ctx, PlanRec &pr)
                 cv_oth[s] = (int)((uint32_t)P.e2n[2 * e + 1 - h] | ((uint32_t)h << 31));
                 cv_own[s] = (uint16_t)(P.e2n[2 * e + h] - c * K);
             }
-        rc = upload(ctx, pr, ce, order ? D.cvf_eid : D.cv_eid);
-        if (!rc) rc = upload(ctx, pr, cv_oth, order ? D.cvf_oth : D.cv_oth);
-        if (!rc) rc = upload(ctx, pr, cv_own, order ? D.cvf_own : D.cv_own);
+        rc = upload(ctx, pr, ce, order == 2 ? D.cve_eid : order ? D.cvf_eid : D.cv_eid);
+        if (!rc) rc = upload(ctx, pr, cv_oth, order == 2 ? D.cve_oth : order ? D.cvf_oth : D.cv_oth);
+        if (!rc) rc = upload(ctx, pr, cv_own, order == 2 ? D.cve_own : order ? D.cvf_own : D.cv_own);
     }
     return rc;
 }
@@ -259,9 +259,9 @@ int upload_fixed(opf_ctx *ctx, PlanRec &pr)
     } else {
         X.iblk = D.iblk;
         X.cv_off = D.cv_off;
-        X.cv_eid = D.cvf_eid;
-        X.cv_oth = D.cvf_oth;
-        X.cv_own = D.cvf_own;
+        X.cv_eid = D.cve_eid;
+        X.cv_oth = D.cve_oth;
+        X.cv_own = D.cve_own;
     }
     X.iw = D.iw;
     if (!rc) rc = upload(ctx, pr, F.rnd_off, X.rnd_off);

@@ -708,8 +708,8 @@ int build_plan(int64_t N, int64_t E, const int32_t *e2n_user, const PlanOptions 
             while (t < pn && P.e2n[2 * (p0 + t)] / K == c && P.e2n[2 * (p0 + t) + 1] / K == c) ++t;
             P.cl_nint[c] = (int32_t)t;
         }
-        std::vector<std::vector<int32_t>> cut_eid(ncl), cutf_eid(ncl);
-        std::vector<std::vector<uint8_t>> cut_end(ncl), cutf_end(ncl);
+        std::vector<std::vector<int32_t>> cut_eid(ncl), cutf_eid(ncl), cute_eid(ncl);
+        std::vector<std::vector<uint8_t>> cut_end(ncl), cutf_end(ncl), cute_end(ncl);
         parallel_for(ncl, [&](int64_t c) {
             std::vector<int64_t> src;
             const int64_t p0 = P.cl_prim[2 * c], pn = P.cl_prim[2 * c + 1];
@@ -724,27 +724,32 @@ int build_plan(int64_t N, int64_t E, const int32_t *e2n_user, const PlanOptions 
                         vh.push_back((uint8_t)h);
                     }
             {
-                // the second order: each run sorted by (foreign node, owned node)
+                // the other orders: each run sorted by (foreign node, owned node), and
+                // by edge
                 const int64_t n = (int64_t)ve.size();
                 auto foreign = [&](int64_t t) { return P.e2n[2 * ve[t] + (1 - vh[t])]; };
                 auto owned = [&](int64_t t) { return P.e2n[2 * ve[t] + vh[t]]; };
-                std::vector<int64_t> idx(n);
-                std::iota(idx.begin(), idx.end(), 0);
-                for (int64_t a = 0; a < n;) {
-                    int64_t b = a + 1;
-                    while (b < n && foreign(b) / K == foreign(a) / K) ++b;
-                    std::stable_sort(idx.begin() + a, idx.begin() + b, [&](int64_t x, int64_t y) {
-                        if (foreign(x) != foreign(y)) return foreign(x) < foreign(y);
-                        return owned(x) < owned(y);
-                    });
-                    a = b;
-                }
-                cutf_eid[c].resize(n);
-                cutf_end[c].resize(n);
-                for (int64_t t = 0; t < n; ++t) {
-                    cutf_eid[c][t] = ve[idx[t]];
-                    cutf_end[c][t] = vh[idx[t]];
-                }
+                auto sorted = [&](const auto &less, std::vector<int32_t> &oe, std::vector<uint8_t> &oh) {
+                    std::vector<int64_t> idx(n);
+                    std::iota(idx.begin(), idx.end(), 0);
+                    for (int64_t a = 0; a < n;) {
+                        int64_t b = a + 1;
+                        while (b < n && foreign(b) / K == foreign(a) / K) ++b;
+                        std::stable_sort(idx.begin() + a, idx.begin() + b, less);
+                        a = b;
+                    }
+                    oe.resize(n);
+                    oh.resize(n);
+                    for (int64_t t = 0; t < n; ++t) {
+                        oe[t] = ve[idx[t]];
+                        oh[t] = vh[idx[t]];
+                    }
+                };
+                sorted([&](int64_t x, int64_t y) {
+                    if (foreign(x) != foreign(y)) return foreign(x) < foreign(y);
+                    return owned(x) < owned(y);
+                }, cutf_eid[c], cutf_end[c]);
+                sorted([&](int64_t x, int64_t y) { return ve[x] < ve[y]; }, cute_eid[c], cute_end[c]);
             }
             if (!opt.bank_spread) return;
             std::vector<int32_t> ends, te;
@@ -779,11 +784,15 @@ int build_plan(int64_t N, int64_t E, const int32_t *e2n_user, const PlanOptions 
         P.cl_cut_end.resize(P.cl_cut_off[ncl]);
         P.cl_cutf_eid.resize(P.cl_cut_off[ncl]);
         P.cl_cutf_end.resize(P.cl_cut_off[ncl]);
+        P.cl_cute_eid.resize(P.cl_cut_off[ncl]);
+        P.cl_cute_end.resize(P.cl_cut_off[ncl]);
         for (int64_t c = 0; c < ncl; ++c) {
             std::copy(cut_eid[c].begin(), cut_eid[c].end(), P.cl_cut_eid.begin() + P.cl_cut_off[c]);
             std::copy(cut_end[c].begin(), cut_end[c].end(), P.cl_cut_end.begin() + P.cl_cut_off[c]);
             std::copy(cutf_eid[c].begin(), cutf_eid[c].end(), P.cl_cutf_eid.begin() + P.cl_cut_off[c]);
             std::copy(cutf_end[c].begin(), cutf_end[c].end(), P.cl_cutf_end.begin() + P.cl_cut_off[c]);
+            std::copy(cute_eid[c].begin(), cute_eid[c].end(), P.cl_cute_eid.begin() + P.cl_cut_off[c]);
+            std::copy(cute_end[c].begin(), cute_end[c].end(), P.cl_cute_end.begin() + P.cl_cut_off[c]);
         }
         P.owner_ok = true;
     }
@@ -975,7 +984,7 @@ void build_fixed(const Plan &P, int K, int NT, FixedLists &F)
                     } else if (F.fine) {
                         see(F.cv_own[s], k - b);
                     } else {
-                        see(P.e2n[2 * (int64_t)P.cl_cutf_eid[s] + P.cl_cutf_end[s]] - v0, k - b);
+                        see(P.e2n[2 * (int64_t)P.cl_cute_eid[s] + P.cl_cute_end[s]] - v0, k - b);
                     }
                 }
             };
@@ -1148,15 +1157,16 @@ VerifyResult verify_plan(const Plan &P, const int32_t *e2n_user)
         }
         // the two loops of the owner kernel cover every end of every edge exactly
         // once: interior blocks both ends, each cut visit the end it names (in
-        // both orders of the cut visits)
+        // every order of the cut visits)
         if ((int64_t)P.cl_nint.size() != ncl || (int64_t)P.cl_cut_off.size() != ncl + 1 ||
             P.cl_cut_off[0] != 0 || P.cl_cut_off[ncl] != (int64_t)P.cl_cut_eid.size() ||
             P.cl_cut_eid.size() != P.cl_cut_end.size() || P.cl_cutf_eid.size() != P.cl_cut_eid.size() ||
-            P.cl_cutf_end.size() != P.cl_cut_eid.size())
+            P.cl_cutf_end.size() != P.cl_cut_eid.size() || P.cl_cute_eid.size() != P.cl_cut_eid.size() ||
+            P.cl_cute_end.size() != P.cl_cut_eid.size())
             return fail(8, -1, "interior blocks or cut visits are inconsistent");
-        for (int order = 0; order < 2; ++order) {
-            const std::vector<int32_t> &ce = order ? P.cl_cutf_eid : P.cl_cut_eid;
-            const std::vector<uint8_t> &ch = order ? P.cl_cutf_end : P.cl_cut_end;
+        for (int order = 0; order < 3; ++order) {
+            const std::vector<int32_t> &ce = order == 2 ? P.cl_cute_eid : order ? P.cl_cutf_eid : P.cl_cut_eid;
+            const std::vector<uint8_t> &ch = order == 2 ? P.cl_cute_end : order ? P.cl_cutf_end : P.cl_cut_end;
             std::vector<uint8_t> ends(E, 0);  // bit h: end h covered
             for (int64_t c = 0; c < ncl; ++c) {
                 const int64_t p0 = P.cl_prim[2 * c], ni = P.cl_nint[c];

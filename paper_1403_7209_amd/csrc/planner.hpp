@@ -98,6 +98,10 @@ struct Plan {
     std::vector<uint8_t> cl_cut_end;
     std::vector<int32_t> cl_cutf_eid;
     std::vector<uint8_t> cl_cutf_end;
+    // And once more with each run in edge order (cl_cute_*): a run's edges are one
+    // range of the edge order, so the edge inputs are read coalesced.
+    std::vector<int32_t> cl_cute_eid;
+    std::vector<uint8_t> cl_cute_end;
     // Flat colouring (one level over all edges; no partitions): edges
     // flat_eid[flat_off[c] .. flat_off[c+1]) have colour c and share no node.
     bool flat_ok = false;  // false when more than 128 colours would be needed
