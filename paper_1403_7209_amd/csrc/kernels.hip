@@ -1161,12 +1161,26 @@ struct FixedPtrs {
     const uint16_t *ent;
 };
 
+// Node g's stage update of component v from its total r and base state; the
+// residual it takes up (see StagePtrs) included, r^2 returned.
+template <typename T, typename B>
+__device__ __forceinline__ double stage_one(const StagePtrs<T> &sp, int v, int g, double r, double step,
+                                            B base)
+{
+    if (sp.res[0]) {
+        r += ld(sp.res[v], g);
+        st(sp.res[v], g, 0.0);
+    }
+    st(sp.q[v], g, (T)((double)base - step * r));
+    return r * r;
+}
+
 // The owner loop with every sum in a fixed order (no LDS atomics): the chunk's
 // visits (interior block, then cut visits) go in rounds of NT, one per thread;
 // each puts its values into an LDS slot, and after a barrier every node adds
 // the slots of its own edges in list order into registers.  The result is the
-// same bit for bit on every run.  KC > 0 fixes the chunk size; with KC < NT the
-// NT / KC threads of a node share its NOUT sums.
+// same bit for bit on every run.  KC > 0 fixes the chunk size (at most NT: a
+// thread sums one node).
 // It serves the coloured variant: against one launch per partition colour, each
 // re-reading and re-writing the nodes' totals with a barrier per edge colour,
 // one launch that writes each total once (FP64 flux of a 1M-node mesh in RCM
@@ -1182,8 +1196,6 @@ __global__ __launch_bounds__(kOwnerThreads, (FixedTune<T, Op>::WAVES)) void k_ed
 {
     constexpr int NT = kOwnerThreads;
     using M = Message<Op>;
-    constexpr int P = NT / (KC > 0 ? KC : NT);       // threads per node
-    constexpr int NV = (Op::NOUT + P - 1) / P;       // sums per thread
     constexpr int NPH = Op::MODE == GEN ? 2 : 1;     // one hand-over per end where they differ
     const int K = KC > 0 ? KC : Kr;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1200,14 +1212,13 @@ __global__ __launch_bounds__(kOwnerThreads, (FixedTune<T, Op>::WAVES)) void k_ed
         load_stage<Op>(a, v0 + v, gamma, rec);
         lds_put<T, Op::NS>(ss, K, v, rec);
     }
-    const int node = P > 1 ? t % K : t, vb = P > 1 ? (t / K) * NV : 0;
-    const bool sums = node < nown && vb < Op::NOUT;
-    double acc[NV];
+    const bool sums = t < nown;
+    double acc[Op::NOUT];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) acc[i] = 0.0;
+    for (int i = 0; i < Op::NOUT; ++i) acc[i] = 0.0;
     __syncthreads();
 
-    auto range = [&](int r) { return sums ? f.off[(size_t)r * K + node] : 0u; };
+    auto range = [&](int r) { return sums ? f.off[(size_t)r * K + t] : 0u; };
     uint32_t rg = n > 0 ? range(r0) : 0u;
     for (int r = r0, b = 0; b < n; ++r, b += NT) {
         // this round's entries of the thread's node, the first few fetched early
@@ -1262,9 +1273,8 @@ __global__ __launch_bounds__(kOwnerThreads, (FixedTune<T, Op>::WAVES)) void k_ed
                 const uint32_t end = e >> 15;
                 if (NPH == 2 && (int)end != ph) return;
 #pragma unroll
-                for (int i = 0; i < NV; ++i) {
-                    if (P > 1 && vb + i >= Op::NOUT) break;
-                    const double y = M::template term<NT>(Y, vb + i, slot);
+                for (int i = 0; i < Op::NOUT; ++i) {
+                    const double y = M::template term<NT>(Y, i, slot);
                     acc[i] += Op::MODE == ANTI ? flip(y, end) : y;
                 }
             };
@@ -1275,41 +1285,119 @@ __global__ __launch_bounds__(kOwnerThreads, (FixedTune<T, Op>::WAVES)) void k_ed
             __syncthreads();
         }
     }
-    const int g = v0 + node;
+    const int g = v0 + t;
     if constexpr (STAGE) {
-        double sq[NV];
-#pragma unroll
-        for (int i = 0; i < NV; ++i) sq[i] = 0.0;
+        double sq[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         if (sums) {
             const double step = (sp.dt ? sp.adt * ld(sp.dt, g) : sp.adt) / ld(sp.vol, g);
 #pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                const int v = vb + i;
-                double r = acc[i];
-                if (sp.res[0]) {
-                    r += ld(sp.res[v], g);
-                    st(sp.res[v], g, 0.0);
-                }
-                sq[i] = r * r;
-                st(sp.q[v], g, (T)((double)ld(sp.q0[v], g) - step * r));
-            }
+            for (int v = 0; v < 6; ++v) sq[v] = stage_one(sp, v, g, acc[v], step, ld(sp.q0[v], g));
         }
-        double *out = sp.partial + 6 * c;
-        if constexpr (P == 1) {
-            lds_sum6(sq, Y, out);
-        } else {
-            static_assert(NV == 1 && KC <= 64, "a sum's nodes are lanes of one wavefront");
-#pragma unroll
-            for (int o = KC / 2; o > 0; o >>= 1) sq[0] += __shfl_down(sq[0], o, KC);
-            if (sums && node == 0) out[vb] = sq[0];
-        }
+        lds_sum6(sq, Y, sp.partial + 6 * c);
     } else if (sums) {
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            if (P > 1 && vb + i >= Op::NOUT) break;
-            double *y = a.y[vb + i];
-            st(y, g, overwrite ? acc[i] : ld(y, g) + acc[i]);
+        for (int i = 0; i < Op::NOUT; ++i)
+            st(a.y[i], g, overwrite ? acc[i] : ld(a.y[i], g) + acc[i]);
+    }
+}
+
+// The same over the small chunks of a small mesh, where one chunk's chain of
+// trips to memory is the loop's time: the chunk's (edge, end) pairs, sorted by
+// node, go one per thread, all loads of a step in flight together and no record
+// staged (both ends' states are gathered); a node's slots are then one range,
+// which the NT / K threads of the node add up, NV of its NOUT sums each.  Three
+// trips to memory (offsets, visits, records) and one barrier: 5.8 us per FP64
+// stage at 8,000 nodes, 250 workgroups on 256 CUs, where staged records and entry
+// lists took 6.6 and sixteen 512-node clusters 13.5.
+struct FinePtrs {
+    const int *off, *eid, *oth;
+    const uint16_t *own;
+    const int *node_off;
+};
+
+template <typename T, class Op, bool STAGE = false>
+__global__ __launch_bounds__(kOwnerThreads) void k_edge_fine(FinePtrs f, Arrays<T> a, T gamma, int N,
+                                                             int nch, int remap, int overwrite,
+                                                             StagePtrs<T> sp = {})
+{
+    constexpr int NT = kOwnerThreads, K = kFixedFine;
+    using M = Message<Op>;
+    constexpr int NV = (Op::NOUT + NT / K - 1) / (NT / K);
+    extern __shared__ __align__(16) unsigned char smem[];
+    double *Y = reinterpret_cast<double *>(smem);
+    const int t = (int)threadIdx.x;
+    const int c = remap ? xcd_map((int)blockIdx.x, nch) : (int)blockIdx.x;
+    const int v0 = c * K, nown = min(K, N - v0);
+    const int s0 = f.off[c], n = f.off[c + 1] - s0;
+    const int node = t % K, vb = (t / K) * NV, g = v0 + node;
+    const bool sums = node < nown && vb < Op::NOUT;
+    // what the sums will need, asked for now
+    int j0 = 0, j1 = 0;
+    double base[NV], vol = 1.0, adt = 1.0;
+    if (sums) {
+        j0 = f.node_off[g] - s0;
+        j1 = f.node_off[g + 1] - s0;
+        if constexpr (STAGE) {
+            vol = ld(sp.vol, g);
+            if (sp.dt) adt = ld(sp.dt, g);
         }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            base[i] = 0.0;
+            if (vb + i < Op::NOUT) {
+                if constexpr (STAGE) base[i] = (double)ld(sp.q0[vb + i], g);
+                else if (!overwrite) base[i] = ld(a.y[vb + i], g);
+            }
+        }
+    }
+    double acc[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) acc[i] = 0.0;
+    for (int b = 0; b < n; b += NT) {
+        const int k = b + t;
+        if (k < n) {
+            const int eid = ld(f.eid, s0 + k), oth = ld(f.oth, s0 + k), own = v0 + (int)ld(f.own, s0 + k);
+            const uint32_t second = (uint32_t)oth >> 31;
+            T w[Op::NW], xa[Op::NIN], xb[Op::NIN], sa[Op::NS], sb[Op::NS];
+#pragma unroll
+            for (int d = 0; d < Op::NW; ++d) w[d] = ld(a.w[d], eid);
+#pragma unroll
+            for (int v = 0; v < Op::NIN; ++v) {
+                xa[v] = ld(a.x[v], own);
+                xb[v] = ld(a.x[v], oth & 0x7fffffff);
+            }
+            Op::stage(xa, sa, gamma);
+            Op::stage(xb, sb, gamma);
+#pragma unroll
+            for (int d = 0; d < Op::NW; ++d) w[d] = flip(w[d], second);
+            double m[M::NM], m2[M::NM], wo[3] = {0.0, 0.0, 0.0};
+            M::type::edge(sa, sb, w, gamma, m, m2, wo);
+            if constexpr (Op::NWOUT > 0) {
+                if (own < (oth & 0x7fffffff)) {  // written once, from the smaller end
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) st(a.wo[d], eid, flip(wo[d], second));
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < M::NM; ++i) Y[i * NT + t] = m[i];
+        }
+        __syncthreads();
+        for (int j = max(j0, b); j < min(j1, b + NT); ++j)
+#pragma unroll
+            for (int i = 0; i < NV; ++i)
+                if (vb + i < Op::NOUT) acc[i] += M::template term<NT>(Y, vb + i, j - b);
+        if (b + NT < n) __syncthreads();
+    }
+    if constexpr (STAGE) {
+        static_assert(NV == 1 && K <= 64, "a sum's nodes are lanes of one wavefront");
+        double sq = sums ? stage_one(sp, vb, g, acc[0], (sp.dt ? sp.adt * adt : sp.adt) / vol, base[0]) : 0.0;
+#pragma unroll
+        for (int o = K / 2; o > 0; o >>= 1) sq += __shfl_down(sq, o, K);
+        if (sums && node == 0) sp.partial[6 * c + vb] = sq;
+    } else if (sums) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+            if (vb + i < Op::NOUT) st(a.y[vb + i], g, base[i] + acc[i]);
     }
 }
 
@@ -1675,13 +1763,11 @@ int run_owner_stage(const DevPlan &P, const EdgeArrays &a, const StagePtrs<T> &s
     return (int)hipGetLastError();
 }
 
-// Chunk sizes fixed at compile time: the default cluster size and the small
-// meshes'.
+// Chunk size fixed at compile time: the default cluster size.
 template <typename T, class Op, bool STAGE = false, class F>
 void fixed_kernels(F &&f)
 {
     f(512, k_edge_fixed<T, Op, 512, STAGE>);
-    f(kFixedFine, k_edge_fixed<T, Op, kFixedFine, STAGE>);
     f(0, k_edge_fixed<T, Op, 0, STAGE>);
 }
 
@@ -1691,12 +1777,26 @@ size_t fixed_lds(int K)
     return stage_bytes<T, Op>(K) + (size_t)Message<Op>::NM * kOwnerThreads * sizeof(double);
 }
 
+template <class Op>
+constexpr size_t fine_lds()
+{
+    return (size_t)Message<Op>::NM * kOwnerThreads * sizeof(double);
+}
+static_assert(fine_lds<OpGrad>() <= 65536, "within the default LDS limit");
+
 template <typename T, class Op, bool STAGE = false>
 int run_fixed(const DevPlan &P, const EdgeArrays &a, double gamma, hipStream_t st, const LaunchOpts &lo,
               const StagePtrs<T> &sp = {})
 {
     const FixedPlan &X = P.fixed;
     if (X.K <= 0) return (int)hipErrorInvalidValue;
+    if (X.fine) {
+        const FinePtrs fp{X.cv_off, X.cv_eid, X.cv_oth, X.cv_own, X.node_off};
+        hipLaunchKernelGGL((k_edge_fine<T, Op, STAGE>), dim3(X.nchunk), dim3(kOwnerThreads),
+                           fine_lds<Op>(), st, fp, typed<T>(a), (T)gamma, P.N, X.nchunk, lo.xcd_remap,
+                           lo.overwrite, sp);
+        return (int)hipGetLastError();
+    }
     const OwnerPtrs op{X.iblk, X.iw, X.cv_off, X.cv_eid, X.cv_oth, X.cv_own};
     const FixedPtrs fp{X.rnd_off, X.ent_base, X.off, X.ent};
     const size_t lds = fixed_lds<T, Op>(X.K);
@@ -1830,13 +1930,15 @@ size_t edge_lds_bytes(int op, bool fp32, int variant, int umax, int K)
     return fp32 ? lds_bytes<float, OpFlux>(rows) : lds_bytes<double, OpFlux>(rows);
 }
 
-size_t fixed_lds_bytes(int op, bool fp32, int K)
+size_t fixed_lds_bytes(int op, bool fp32, const FixedPlan &X)
 {
-    if (op == OP_ADJOINT) return fixed_lds<double, OpAdjoint>(K);
-    if (op == OP_GRAD) return fixed_lds<double, OpGrad>(K);
-    if (op == OP_FLUX2) return fixed_lds<double, OpFlux2>(K);
-    if (op == OP_SPECRAD) return fp32 ? fixed_lds<float, OpSpecrad>(K) : fixed_lds<double, OpSpecrad>(K);
-    return fp32 ? fixed_lds<float, OpFlux>(K) : fixed_lds<double, OpFlux>(K);
+    if (X.fine) return fine_lds<OpGrad>();  // the largest
+    if (op == OP_ADJOINT) return fixed_lds<double, OpAdjoint>(X.K);
+    if (op == OP_GRAD) return fixed_lds<double, OpGrad>(X.K);
+    if (op == OP_FLUX2) return fixed_lds<double, OpFlux2>(X.K);
+    if (op == OP_SPECRAD)
+        return fp32 ? fixed_lds<float, OpSpecrad>(X.K) : fixed_lds<double, OpSpecrad>(X.K);
+    return fp32 ? fixed_lds<float, OpFlux>(X.K) : fixed_lds<double, OpFlux>(X.K);
 }
 
 int set_lds_limit(size_t bytes)

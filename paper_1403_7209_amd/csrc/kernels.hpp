@@ -28,12 +28,14 @@ __device__ __forceinline__ int xcd_map(int k, int n)
     return x * per + min(x, rem) + i;
 }
 
-// Lists of the fixed-order owner loop (k_edge_fixed): chunk c owns the internal
-// nodes [c K, (c+1) K) and runs its interior block, then its cut visits, in
-// rounds of kOwnerThreads visits (rounds rnd_off[c] .. rnd_off[c+1]).  In round
-// r node k of the chunk adds up the entries ent[ent_base[r] + off[r (K+1) + k]
-// .. ent_base[r] + off[r (K+1) + k + 1]): the visit's slot in the round, bit 15
-// set when the node is the second end of an interior edge.
+// Lists of the fixed-order owner loops: chunk c owns the internal nodes [c K,
+// (c+1) K).  k_edge_fixed runs its interior block, then its cut visits, in rounds
+// of kOwnerThreads visits (rounds rnd_off[c] .. rnd_off[c+1]).  In round r node k
+// of the chunk adds up the entries ent[ent_base[r] + i] with i from the low to
+// below the high half of off[r K + k]: the visit's slot in the round, bit 15 set
+// when the node is the second end of an interior edge.  k_edge_fine (fine) runs
+// the chunk's (edge, end) pairs cv_off[c] .. cv_off[c+1], which are sorted by
+// owned node: node i's are node_off[i] .. node_off[i+1].
 struct FixedPlan {
     int K = 0, nchunk = 0;  // K = 0: no lists
     bool fine = false;      // chunks smaller than the owner clusters
@@ -41,6 +43,7 @@ struct FixedPlan {
     const uint32_t *iw = nullptr;
     const int *cv_off = nullptr, *cv_eid = nullptr, *cv_oth = nullptr;
     const uint16_t *cv_own = nullptr;
+    const int *node_off = nullptr;
     const int *rnd_off = nullptr, *ent_base = nullptr;
     const uint32_t *off = nullptr;
     const uint16_t *ent = nullptr;
@@ -50,7 +53,7 @@ constexpr int kFixedMaxK = kOwnerThreads;
 // The chunk of a small mesh, the most nodes of one (see fixed_chunk), and the
 // most for which the owner variant takes it (see takes_fixed).
 constexpr int kFixedFine = 32;
-constexpr int kFixedFineNodes = 65536;
+constexpr int kFixedFineNodes = 98304;
 constexpr int kFixedFineOwner = 24576;
 // Stages of one iteration.
 constexpr int kStages = 5;
@@ -275,8 +278,8 @@ int launch_local_dt(int N, const double *vol, const double *lam, double cfl, dou
 // LDS bytes (dynamic and static) of one workgroup of an edge loop.
 size_t edge_lds_bytes(int op, bool fp32, int variant, int umax, int K);
 
-// LDS bytes of one workgroup of the fixed-order loop over chunks of K nodes.
-size_t fixed_lds_bytes(int op, bool fp32, int K);
+// LDS bytes of one workgroup of the plan's fixed-order loop.
+size_t fixed_lds_bytes(int op, bool fp32, const FixedPlan &X);
 
 // Lets every edge kernel instance use up to `bytes` of LDS in total.
 int set_lds_limit(size_t bytes);

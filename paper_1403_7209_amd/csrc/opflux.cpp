@@ -225,11 +225,11 @@ int upload_owner(opf_ctx *ctx, PlanRec &pr)
 }
 
 // Nodes per chunk of the fixed-order loop: the owner clusters' size, or 32 up to
-// 65,536 nodes.  There 512-node chunks number at most 128, a workgroup each on
+// 98,304 nodes.  There 512-node chunks number at most 192, a workgroup each on
 // 256 CUs, and a chunk's 11 rounds follow one another; 32-node chunks run every
-// edge from both ends but take one round each.  Five stages of the FP64 flux
-// with 512- and 32-node chunks: 8,000 nodes 227 and 111 us, 46,656 nodes 247 and
-// 181 us; 216,000 nodes 370 and 648 us (all with a separate stage update).
+// edge from both ends but take one round each.  Five fused stages of the FP64
+// flux in RCM order with 512- and 32-node chunks: 91,125 nodes 171 and 160 us,
+// 117,649 nodes 175 and 195 us.
 int fixed_chunk(const opf::Plan &P)
 {
     const int K = P.cluster_size;
@@ -250,27 +250,26 @@ int upload_fixed(opf_ctx *ctx, PlanRec &pr)
     opf::build_fixed(pr.host, K, opf::gpu::kOwnerThreads, F);
     int rc = OPF_OK;
     if (F.fine) {
-        std::vector<int2> iblk(F.iblk.size() / 2, make_int2(0, 0));
-        rc = upload(ctx, pr, iblk, X.iblk);
-        if (!rc) rc = upload(ctx, pr, F.cv_off, X.cv_off);
+        rc = upload(ctx, pr, F.cv_off, X.cv_off);
         if (!rc) rc = upload(ctx, pr, F.cv_eid, X.cv_eid);
         if (!rc) rc = upload(ctx, pr, F.cv_oth, X.cv_oth);
         if (!rc) rc = upload(ctx, pr, F.cv_own, X.cv_own);
+        if (!rc) rc = upload(ctx, pr, F.node_off, X.node_off);
     } else {
         X.iblk = D.iblk;
+        X.iw = D.iw;
         X.cv_off = D.cv_off;
         X.cv_eid = D.cve_eid;
         X.cv_oth = D.cve_oth;
         X.cv_own = D.cve_own;
+        rc = upload(ctx, pr, F.rnd_off, X.rnd_off);
+        if (!rc) rc = upload(ctx, pr, F.ent_base, X.ent_base);
+        if (!rc) rc = upload(ctx, pr, F.off, X.off);
+        if (!rc) rc = upload(ctx, pr, F.ent, X.ent);
     }
-    X.iw = D.iw;
-    if (!rc) rc = upload(ctx, pr, F.rnd_off, X.rnd_off);
-    if (!rc) rc = upload(ctx, pr, F.ent_base, X.ent_base);
-    if (!rc) rc = upload(ctx, pr, F.off, X.off);
-    if (!rc) rc = upload(ctx, pr, F.ent, X.ent);
     X.K = K;
     X.fine = F.fine;
-    X.nchunk = (int)(F.rnd_off.size() - 1);
+    X.nchunk = (int)((pr.host.N + K - 1) / K);
     return rc;
 }
 
@@ -525,8 +524,8 @@ int check_gbl_disjoint(opf_ctx *ctx, const void *p, size_t bytes, std::initializ
 // coloured variant wherever there are any (the same fixed order on every run,
 // without a launch per partition colour); the owner variant up to 24,576 nodes,
 // where its few clusters take as long as one of them does: flux and adjoint at
-// 8,000 nodes 6.3 and 8.5 us against 11.2 and 14.4 over the clusters, at 21,952
-// 9.9 and 16.6 against 11.7 and 15.4, at 46,656 17.0 and 27.4 against 12.2 and
+// 8,000 nodes 5.5 and 7.5 us against 11.2 and 14.4 over the clusters, at 21,952
+// 8.8 and 12.7 against 11.7 and 15.4, at 46,656 14.2 and 21.9 against 12.2 and
 // 16.4.
 bool takes_fixed(const PlanRec &pr, int variant)
 {
@@ -659,7 +658,7 @@ int edge_loop(opf_ctx *ctx, int kernel, opf_set s, int nargs, const opf_arg *arg
             return ctx->fail(OPF_EINVAL, "a workgroup needs " + std::to_string(lds) +
                                              " B of LDS; use a smaller block or cluster size");
         if (takes_fixed(pr, variant)) {
-            const size_t fl = opf::gpu::fixed_lds_bytes(op, fp32, pr.dev.fixed.K);
+            const size_t fl = opf::gpu::fixed_lds_bytes(op, fp32, pr.dev.fixed);
             lo.fixed = fl <= ctx->max_lds ? 1 : 0;
             if (lo.fixed) lds = fl;
         }
@@ -1996,7 +1995,7 @@ int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat
         return ctx->fail(OPF_EINVAL, "a workgroup needs " + std::to_string(lds) + " B of LDS");
     opf::gpu::LaunchOpts lo;
     lo.fixed = takes_fixed(pr, how.variant) ? 1 : 0;
-    if (lo.fixed) lds = opf::gpu::fixed_lds_bytes(opf::gpu::OP_FLUX, fp32, pr.dev.fixed.K);
+    if (lo.fixed) lds = opf::gpu::fixed_lds_bytes(opf::gpu::OP_FLUX, fp32, pr.dev.fixed);
     if (lds > ctx->lds_limit) {
         int e = opf::gpu::set_lds_limit(ctx->max_lds);
         if (e) return hip_fail(ctx, (hipError_t)e, "raising the LDS limit");

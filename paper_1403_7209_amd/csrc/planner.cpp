@@ -949,6 +949,10 @@ void build_fixed(const Plan &P, int K, int NT, FixedLists &F)
                 F.cv_oth[s] = (int32_t)((uint32_t)P.e2n[2 * e + 1 - h] | ((uint32_t)h << 31));
                 F.cv_own[s] = (uint16_t)(v % K);
             }
+        // at[v] is now past node v's last visit
+        F.node_off.assign(P.N + 1, 0);
+        for (int64_t v = 0; v < P.N; ++v) F.node_off[v + 1] = (int32_t)at[v];
+        return;
     }
     F.rnd_off.assign(nch + 1, 0);
     for (int64_t c = 0; c < nch; ++c) {
@@ -981,8 +985,6 @@ void build_fixed(const Plan &P, int K, int NT, FixedLists &F)
                     if (k < ni) {
                         see(P.e2n[2 * (i0 + k)] - v0, k - b);
                         see(P.e2n[2 * (i0 + k) + 1] - v0, (k - b) | 0x8000);
-                    } else if (F.fine) {
-                        see(F.cv_own[s], k - b);
                     } else {
                         see(P.e2n[2 * (int64_t)P.cl_cute_eid[s] + P.cl_cute_end[s]] - v0, k - b);
                     }

@@ -123,10 +123,11 @@ int build_plan(int64_t N, int64_t E, const int32_t *e2n, const PlanOptions &opt,
 // node the slots of the round to add up, in visit order.
 struct FixedLists {
     int32_t K = 0;
-    bool fine = false;  // chunks smaller than the owner clusters, visits of their own
-    std::vector<int32_t> iblk;               // [2 nchunk] (first edge, count); fine: zeros
+    bool fine = false;  // chunks smaller than the owner clusters, visits of their own, no rounds
+    std::vector<int32_t> iblk;               // [2 nchunk] (first edge, count)
     std::vector<int32_t> cv_off, cv_eid, cv_oth;  // fine: every (edge, end) pair by owned node
     std::vector<uint16_t> cv_own;
+    std::vector<int32_t> node_off;  // fine: [N+1] each node's visits
     std::vector<int32_t> rnd_off;   // [nchunk+1] rounds of each chunk
     std::vector<int32_t> ent_base;  // [rounds+1] first entry of each round
     std::vector<uint32_t> off;      // [rounds][K] each node's entries in the round: first |

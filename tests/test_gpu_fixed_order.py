@@ -2,7 +2,7 @@
 owner variant) against the oracle, at the edges of its chunks and rounds:
 meshes of fewer nodes than a chunk, of one chunk more, with a last chunk of one
 node, at both sides of the small-mesh limits (24,576 nodes for the owner variant,
-65,536 for the coloured one), cluster sizes with and without a compile-time
+98,304 for the coloured one), cluster sizes with and without a compile-time
 instance, and a node with more edges than a round has visits.  Results must be the same bits on every run."""
 import numpy as np
 import pytest
@@ -58,11 +58,11 @@ CASES = {  # graph, cluster size, variants
     "fine-33-of-64": (lambda: chain(65), 64, (pk.COLOURED, pk.OWNER)),
     "fine-box11": (lambda: box(11), 512, (pk.COLOURED, pk.OWNER)),
     "owner-limit": (lambda: chain(24576), 512, (pk.COLOURED, pk.OWNER)),
-    "fine-limit": (lambda: chain(65536), 512, (pk.COLOURED,)),
-    "above-limit": (lambda: chain(65537), 512, (pk.COLOURED,)),
-    "run-time-chunk": (lambda: chain(65537), 200, (pk.COLOURED,)),
-    "box41-of-64": (lambda: box(41), 64, (pk.COLOURED,)),
-    "box41": (lambda: box(41), 512, (pk.COLOURED,)),
+    "fine-limit": (lambda: chain(98304), 512, (pk.COLOURED,)),
+    "above-limit": (lambda: chain(98305), 512, (pk.COLOURED,)),
+    "run-time-chunk": (lambda: chain(98305), 200, (pk.COLOURED,)),
+    "box47-of-64": (lambda: box(47), 64, (pk.COLOURED,)),
+    "box47": (lambda: box(47), 512, (pk.COLOURED,)),
     # no two-level colouring: only the owner variant
     "star": (lambda: star(1500), 512, (pk.OWNER,)),
 }
@@ -122,7 +122,7 @@ def test_loops_and_iteration(name):
             assert close(p, r, res)
 
 
-@pytest.mark.parametrize("N", [24577, 65536, 131072, 131073])
+@pytest.mark.parametrize("N", [24577, 65536, 98304, 131072, 131073])
 def test_owner_workgroup_widths(N):
     """The owner variant above the small-mesh limit and on both sides of one
     workgroup per CU (256 clusters; 128 for the gradient's two halves)."""
