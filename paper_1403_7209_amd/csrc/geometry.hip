@@ -21,6 +21,8 @@
 // reverse).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace opf {
@@ -418,8 +420,9 @@ __device__ __forceinline__ void geo_get(const double *X, int L, uint32_t l, doub
     x[2] = X[2 * L + l];
 }
 
-// The edges of a chunk go in batches of kGeoThreads, one per thread; each
-// batch's ring entries (one contiguous run) are first copied to LDS by the
+// The edges of a chunk go in batches of kGeoThreads, one per thread (workgroup
+// blockIdx.y of gridDim.y taking every gridDim.y-th batch); each batch's ring
+// entries (one contiguous run) are first copied to LDS by the
 // whole workgroup, so that the walks read LDS only.  Around edge (a, b) with
 // chain c_0 .. c_k and d_i = x_(c_i) - x_a, tet i contributes
 // (d_(i-1) + d_i - d_b) x (d_i - d_(i-1)) / 24 = (2 d_(i-1) x d_i
@@ -452,8 +455,10 @@ __global__ __launch_bounds__(kGeoThreads) void k_geo_rings(TetArrays a, double p
             if (j < nq) pre[u] = ring32[q0 + j];
         }
     };
+    const int first = (int)blockIdx.y * kGeoThreads, step = (int)gridDim.y * kGeoThreads;
+    if (first >= ce.y) return;
     int q0 = 0, nq = 0;
-    if (ce.y > 0) fetch(0, q0, nq);
+    fetch(first, q0, nq);
     for (int l = t; l < nown + nh; l += kGeoThreads) {
         const bool own = l < nown;
         const int g = own ? v0 + l : a.halo[h0 + l - nown];
@@ -463,7 +468,7 @@ __global__ __launch_bounds__(kGeoThreads) void k_geo_rings(TetArrays a, double p
     }
     const bool wrap = period > 0.0;
     const double ip = wrap ? 1.0 / period : 0.0;
-    for (int b0 = 0; b0 < ce.y; b0 += kGeoThreads) {
+    for (int b0 = first; b0 < ce.y; b0 += step) {
         const int nb = min(kGeoThreads, ce.y - b0), eb = ce.x + b0;
         const int sh = 2 * q0;  // entry o of this batch sits at R16[o - sh]
         const bool act = t < nb;
@@ -484,7 +489,7 @@ __global__ __launch_bounds__(kGeoThreads) void k_geo_rings(TetArrays a, double p
             if (j < nq) R32[j] = pre[u];
         }
         __syncthreads();
-        if (b0 + kGeoThreads < ce.y) fetch(b0 + kGeoThreads, q0, nq);
+        if (b0 + step < ce.y) fetch(b0 + step, q0, nq);
         if (!act) continue;
         double xa[3], xb[3], db[3], d0[3], dp[3];
         geo_get(X, L, R16[o0], xa);
@@ -707,6 +712,17 @@ __global__ __launch_bounds__(kLinkThreads, 6) void k_link_reverse(TetArrays a, d
     }
 }
 
+// Workgroups per chunk of the ring kernel, each taking every so many batches and
+// staging the chunk's coordinates for itself: as many as bring the launch to 1024
+// workgroups, at most 8 (a chunk has about 7 batches).  One, two, four and eight
+// per chunk: 16 chunks (8,000 nodes) 31, 22, 18 and 17 us with the volumes, 178
+// chunks 37, 30, 28 and 28, 512 chunks 49, 47, 48 and 49, 1000 chunks 82, 79, 86
+// and 98, 1954 chunks 153, 157, 170 and 196.
+int ring_groups(int nchunk)
+{
+    return std::min(8, (1024 + nchunk - 1) / nchunk);
+}
+
 }  // namespace
 
 int launch_geometry(bool adjoint, bool gather, int T, const TetArrays &a, double period,
@@ -736,7 +752,7 @@ int launch_geometry(bool adjoint, bool gather, int T, const TetArrays &a, double
                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
                 if (e != hipSuccess) return (int)e;
             }
-            hipLaunchKernelGGL(k_geo_rings, dim3(a.nchunk), dim3(kGeoThreads), lds, st, a, period);
+            hipLaunchKernelGGL(k_geo_rings, dim3(a.nchunk, ring_groups(a.nchunk)), dim3(kGeoThreads), lds, st, a, period);
             hipLaunchKernelGGL(k_geo_vol, dim3(a.nchunk), dim3(kGeoVolThreads),
                                (size_t)a.DV * sizeof(double), st, a);
         } else {
