@@ -100,16 +100,20 @@ typedef enum {
 
 /* How an indirect (edge) loop resolves its increments. */
 typedef enum {
-    OPF_V_COLOURED = 0, /* mini-partitions staged in LDS, edge colours serialised
-                           inside a partition, one launch per partition colour
-                           (Sec. 4.1); deterministic                              */
+    OPF_V_COLOURED = 0, /* the plan of Sec. 4.1; deterministic.  Where the plan
+                           has owner clusters of at most 512 nodes, a single
+                           launch over them whose sums run in a fixed order;
+                           else mini-partitions staged in LDS, edge colours
+                           serialised inside a partition, one launch per
+                           partition colour                                       */
     OPF_V_ATOMIC = 1,   /* one thread per edge, FP64 atomic adds to HBM          */
     OPF_V_OWNER = 2,    /* one workgroup per cluster of consecutive nodes runs
                            every edge touching the cluster (edges between two
                            clusters run twice) and writes its nodes' totals
                            once; single launch, no colours (owner-compute as in
                            Sec. 3.2, at workgroup level).  LDS accumulation uses
-                           FP64 LDS atomics, so the summation order varies      */
+                           FP64 LDS atomics, so the summation order varies
+                           (on meshes of up to 24,576 nodes it is fixed)        */
     OPF_V_COLOURED_LDS_ATOMIC = 3, /* as COLOURED, with LDS atomics in place
                            of the edge colours inside a partition               */
     OPF_V_FLAT = 4      /* one level of colours over the whole edge set (no
@@ -405,9 +409,10 @@ typedef struct {
  *   (signed from the edge's first to its second node) and a quarter of its
  *   volume to each vertex.  period > 0: vertices are unwrapped to the image
  *   nearest vertex 0 in a periodic box of that side.
- *  GEOMETRY_ADJ over tets (ATOMIC, or OWNER: one thread per tet writes its
- *  four vertex shares to the per-tet buffer, ordered node by node, and each
- *  node sums its run in a fixed order): (x, ALL, t2n, 3, READ)
+ *  GEOMETRY_ADJ over tets (ATOMIC, or OWNER: each node sums over the edges in
+ *  whose ring of tets it stands, in a fixed order; on a mesh with a boundary one
+ *  thread per tet writes its four vertex shares to a buffer, ordered node by
+ *  node, and each node sums its run): (x, ALL, t2n, 3, READ)
  *     (wbar, ALL, t2e, 3, READ) (volbar, ALL, t2n, 1, READ)
  *     (xbar, ALL, t2n, 3, INC) gbl period
  *   xbar += (dw/dx)^T wbar + (dvol/dx)^T volbar (shape sensitivities when

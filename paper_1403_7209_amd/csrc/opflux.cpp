@@ -15,6 +15,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -1312,7 +1313,12 @@ int tet_loop(opf_ctx *ctx, int kernel, opf_set s, int nargs, const opf_arg *args
     opf::gpu::TetArrays ta;
     if (gather) {
         DevTetInverse *inv = nullptr;
-        rc = tet_inverse(ctx, t2n, t2e, it->second->host, inv);
+        try {
+            rc = tet_inverse(ctx, t2n, t2e, it->second->host, inv);
+        } catch (const std::bad_alloc &) {
+            free_tinv(ctx, ctx->tinv[std::make_pair((int)t2n, (int)t2e)]);
+            rc = ctx->fail(OPF_ENOMEM, "out of host memory building the tet incidence");
+        }
         if (!rc) {
             ta.t2n = inv->t2n;
             ta.t2e = inv->t2e;
@@ -1656,7 +1662,12 @@ int opf_plan(opf_ctx *ctx, opf_map map, const opf_plan_opts *opts, opf_plan_info
         ctx->plans.erase(old);
     }
     if (ctx->device >= 0) {
-        rc = upload_plan(ctx, *pr);
+        try {
+            rc = upload_plan(ctx, *pr);
+        } catch (const std::bad_alloc &) {
+            free_plan(ctx, *pr);
+            rc = ctx->fail(OPF_ENOMEM, "out of host memory while planning");
+        }
         if (rc) return rc;
     }
     double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();

@@ -5,7 +5,9 @@
 #include <atomic>
 #include <chrono>
 #include <cstdlib>
+#include <new>
 #include <numeric>
+#include <system_error>
 #include <thread>
 
 #include "opflux.h"
@@ -171,12 +173,23 @@ void parallel_for(int64_t n, const F &f)
         return;
     }
     std::atomic<int64_t> next(0);
-    std::vector<std::thread> pool;
-    for (int64_t t = 0; t < nt; ++t)
-        pool.emplace_back([&] {
+    std::atomic<bool> failed(false);
+    auto work = [&] {
+        try {
             for (int64_t i; (i = next.fetch_add(1)) < n;) f(i);
-        });
+        } catch (...) {  // out of memory: nothing else here throws
+            failed = true;
+        }
+    };
+    std::vector<std::thread> pool;
+    pool.reserve(nt);
+    try {
+        for (int64_t t = 1; t < nt; ++t) pool.emplace_back(work);
+    } catch (const std::system_error &) {  // fewer threads then
+    }
+    work();
     for (std::thread &th : pool) th.join();
+    if (failed) throw std::bad_alloc();
 }
 
 // Bank spreading.  The owner kernel's lanes take a cluster's visits in order;
