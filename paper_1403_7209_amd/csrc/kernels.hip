@@ -6,13 +6,16 @@
 // record once per node (state and primitives: velocity, sound speed; the
 // flux rebuilds the pressure as rho c^2 / gamma), so the per-edge work needs
 // no division or square root besides |n_e|.
-// Four ways to resolve the increments:
-//   * coloured (Sec. 4.1): one workgroup per mini-partition, one launch per
-//     partition colour.  The partition's distinct nodes are staged in LDS (the
-//     Sec. 4.1.2 staging; gfx950 has 160 KB of LDS per CU), increments go into
-//     an LDS accumulator one edge colour at a time (or with LDS FP64 atomics in
-//     the ablation variant), then the partition adds its accumulator to HBM
-//     with plain read-modify-write: partitions of one colour share no node.
+// Ways to resolve the increments:
+//   * coloured (Sec. 4.1), the deterministic one: where the plan has owner
+//     clusters, one workgroup per cluster with every sum in a fixed order
+//     (k_edge_fixed, or k_edge_fine over the small chunks of a small mesh); else
+//     one workgroup per mini-partition, one launch per partition colour.  The
+//     partition's distinct nodes are then staged in LDS (the Sec. 4.1.2 staging;
+//     gfx950 has 160 KB of LDS per CU), increments go into an LDS accumulator one
+//     edge colour at a time (or with LDS FP64 atomics in the ablation variant),
+//     and the partition adds its accumulator to HBM with plain read-modify-write:
+//     partitions of one colour share no node.
 //   * atomic: one thread per edge, FP64 atomic adds straight to HBM.
 //   * flat: one level of edge colours over the whole mesh, one launch per
 //     colour, one thread per edge, plain read-add-write in HBM (the
@@ -1675,6 +1678,10 @@ bool owner_streams(const DevPlan &P, bool stage)
 // -> 55; with more workgroups than CUs they no longer share one: 262,144 nodes,
 // FP64 113 -> 129 us).
 constexpr int kOwnerWide = 1024, kOwnerWideGrid = 256;
+// And of 768 threads, two to a CU, for the flux up to 512 clusters (five fused
+// stages, a share of 184,857 nodes: FP64 107 -> 104 us, FP32 93 -> 88.5; 262,144
+// nodes: 107 -> 104 and 91 -> 87; 300,000 nodes, 586 clusters: no gain).
+constexpr int kOwnerMid = 768, kOwnerMidGrid = 512;
 template <typename T, class O>
 constexpr bool owner_wide()
 {
@@ -1687,7 +1694,7 @@ void launch_owner_kc(bool hint, int grid, size_t lds, hipStream_t st, const Owne
                      const Arrays<T> &a, T gamma, const DevPlan &P, const LaunchOpts &lo,
                      int overwrite, const StagePtrs<T> &sp)
 {
-    if constexpr (OwnerTune<T, O>::STREAM) {
+    if constexpr (OwnerTune<T, O>::STREAM && NT == OwnerTune<T, O>::NT) {
         if (hint) {
             hipLaunchKernelGGL((k_edge_owner<T, O, NT, KC, STAGE, H, true>), dim3(grid), dim3(NT),
                                lds, st, op, a, gamma, P.N, P.K, P.ncl, lo.xcd_remap, overwrite, sp);
@@ -1707,6 +1714,13 @@ void launch_owner(bool hint, int grid, size_t lds, hipStream_t st, const OwnerPt
         if (P.K == kOwnerKC && grid <= kOwnerWideGrid) {
             launch_owner_kc<T, O, kOwnerWide, kOwnerKC, STAGE, H>(false, grid, lds, st, op, a, gamma, P,
                                                                   lo, overwrite, sp);
+            return;
+        }
+    }
+    if constexpr (std::is_same<O, OpFlux>::value) {
+        if (P.K == kOwnerKC && grid <= kOwnerMidGrid) {
+            launch_owner_kc<T, O, kOwnerMid, kOwnerKC, STAGE, H>(false, grid, lds, st, op, a, gamma, P,
+                                                                 lo, overwrite, sp);
             return;
         }
     }
@@ -1865,6 +1879,12 @@ int raise_owner(size_t bytes)
         if (!rc)
             rc = raise_one(
                 reinterpret_cast<const void *>(&k_edge_owner<T, O, kOwnerWide, kOwnerKC, STAGE, H, false>),
+                bytes);
+    }
+    if constexpr (std::is_same<O, OpFlux>::value) {
+        if (!rc)
+            rc = raise_one(
+                reinterpret_cast<const void *>(&k_edge_owner<T, O, kOwnerMid, kOwnerKC, STAGE, H, false>),
                 bytes);
     }
     if constexpr (OwnerTune<T, O>::STREAM) {
