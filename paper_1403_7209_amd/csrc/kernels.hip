@@ -402,6 +402,9 @@ struct OpFlux2 {
 // less than in foreign order) and the fixed-order loops (3 %).  SPREAD (the owned
 // ends of 16 visits in distinct LDS banks): the FP32 flux and the gradient, bound
 // by their LDS updates (edge order costs the FP32 flux 2 %).
+// EARLY: the next round's cut visits are read while this one's records are
+// gathered.  The FP64 flux gains (2.1M nodes 1 %, a share of 184,857 nodes 3 %);
+// the adjoint, at its limit of registers, loses 2.5 % and the others up to 0.5 %.
 // STREAM: non-temporal hints on the loop's once-touched data (ld1/st1) when
 // its arrays exceed the last-level cache (owner_streams).  They pay in the
 // flux loops (3-5 %) and cost in the adjoint, gradient and second-order loops
@@ -412,6 +415,7 @@ enum CutOrder { SPREAD, FOREIGN, EDGE };
 template <typename T, class Op>
 struct OwnerTune {
     static constexpr int B = 2, BC = 2, WAVES = 0, NT = kOwnerThreads;
+    static constexpr bool EARLY = false;
     static constexpr CutOrder ORDER = SPREAD;
     static constexpr bool STREAM = false;
 };
@@ -419,6 +423,7 @@ template <>
 struct OwnerTune<float, OpFlux> {
     static constexpr int B = OPF_FLUX32_BATCH, BC = OPF_FLUX32_CUT_BATCH, WAVES = OPF_FLUX32_WAVES,
                          NT = kOwnerThreads;
+    static constexpr bool EARLY = false;
     static constexpr CutOrder ORDER = SPREAD;
     static constexpr bool STREAM = true;
 };
@@ -426,6 +431,7 @@ template <>
 struct OwnerTune<double, OpFlux> {
     static constexpr int B = OPF_FLUX64_BATCH, BC = OPF_FLUX64_CUT_BATCH, WAVES = OPF_FLUX64_WAVES,
                          NT = kOwnerThreads;
+    static constexpr bool EARLY = true;
     static constexpr CutOrder ORDER = EDGE;
     static constexpr bool STREAM = true;
 };
@@ -433,12 +439,14 @@ template <>
 struct OwnerTune<double, OpAdjoint> {
     static constexpr int B = OPF_ADJ_BATCH, BC = OPF_ADJ_CUT_BATCH, WAVES = OPF_ADJ_WAVES,
                          NT = kOwnerThreads;
+    static constexpr bool EARLY = false;
     static constexpr CutOrder ORDER = FOREIGN;
     static constexpr bool STREAM = false;
 };
 template <>
 struct OwnerTune<double, OpGradH> {
     static constexpr int B = OPF_GRAD_BATCH, BC = OPF_GRAD_BATCH, WAVES = 0, NT = OPF_GRAD_THREADS;
+    static constexpr bool EARLY = false;
     static constexpr CutOrder ORDER = SPREAD;
     static constexpr bool STREAM = false;
 };
@@ -458,6 +466,7 @@ template <>
 struct OwnerTune<double, OpFlux2> {
     static constexpr int B = OPF_FLUX2_BATCH, BC = OPF_FLUX2_CUT_BATCH, WAVES = 0,
                          NT = OPF_FLUX2_THREADS;
+    static constexpr bool EARLY = false;
     static constexpr CutOrder ORDER = FOREIGN;
     static constexpr bool STREAM = false;
 };
@@ -1009,8 +1018,10 @@ __global__ __launch_bounds__(NT, (owner_waves<T, Op, NT>())) void k_edge_owner(
             }
         }
     };
-    visits(threadIdx.x);
+    constexpr bool EARLY = OwnerTune<T, Op>::EARLY;
+    if constexpr (EARLY) visits(threadIdx.x);
     for (int k0 = threadIdx.x; k0 < ns; k0 += NT * BC) {
+        if constexpr (!EARLY) visits(k0);
         int eid[BC], oth[BC], own[BC];
 #pragma unroll
         for (int b = 0; b < BC; ++b) {
@@ -1028,7 +1039,7 @@ __global__ __launch_bounds__(NT, (owner_waves<T, Op, NT>())) void k_edge_owner(
 #pragma unroll
             for (int v = 0; v < Op::NIN; ++v) xf[b][v] = ld(a.x[v], g);
         }
-        visits(k0 + NT * BC);
+        if constexpr (EARLY) visits(k0 + NT * BC);
 #pragma unroll
         for (int b = 0; b < BC; ++b) {
             if (eid[b] < 0) continue;
