@@ -2076,18 +2076,21 @@ int opf_rk_iteration(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_da
         return ctx->fail(OPF_EINVAL, "the iteration runs as OWNER or COLOURED");
     if ((res >= 0) != (variant == OPF_V_COLOURED))
         return ctx->fail(OPF_EINVAL, "the COLOURED iteration takes a residual, the OWNER one none");
-    if (!ctx->dat_ok(qb) || !ctx->dat_ok(qc)) return ctx->fail(OPF_EINVAL, "invalid dat handle");
+    for (opf_dat d : {q, n, vol, qb, qc})
+        if (!ctx->dat_ok(d)) return ctx->fail(OPF_EINVAL, "invalid dat handle");
+    for (opf_dat d : {dt, res})
+        if (d >= 0 && !ctx->dat_ok(d)) return ctx->fail(OPF_EINVAL, "invalid dat handle");
     int rc = check_gbl_disjoint(ctx, ss_dev, 6 * S * sizeof(double), {q, n, vol, dt, qb, qc, res},
                                 "iteration ss");
     if (!rc) rc = check_disjoint(ctx, qc, {q, qb, n, vol, dt, res}, "iteration qc");
     if (rc) return rc;
     auto it = ctx->plans.find(e2n);
     if (it == ctx->plans.end()) return ctx->fail(OPF_ESTATE, "no plan for this map: call opf_plan");
+    rc = device_ready(ctx);
+    if (rc) return rc;
     if (variant == OPF_V_COLOURED && (!it->second->host.coloured_ok || !takes_fixed(*it->second, variant)))
         return ctx->fail(OPF_EINVAL, "the plan has no fixed-order lists (a two-level colouring and "
                                      "clusters of at most 512 nodes are needed)");
-    rc = device_ready(ctx);
-    if (rc) return rc;
     const hipStream_t st = static_cast<hipStream_t>(stream);
     rc = scratch_begin(ctx, st);
     if (rc) return rc;
