@@ -120,6 +120,15 @@ __device__ __forceinline__ double tsqrt(double x)
     return fma(g, fma(-g, h, 0.5), g);
 }
 __device__ __forceinline__ float tsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
+__device__ __forceinline__ double tfma(double a, double b, double c) { return fma(a, b, c); }
+__device__ __forceinline__ float tfma(float a, float b, float c) { return fmaf(a, b, c); }
+// a . b, which of its products are rounded being fixed.
+template <typename T>
+__device__ __forceinline__ T dot3(const T *a, const T *b)
+{
+#pragma clang fp contract(off)
+    return tfma(a[2], b[2], tfma(a[0], b[0], a[1] * b[1]));
+}
 __device__ __forceinline__ double tabs(double x) { return fabs(x); }
 __device__ __forceinline__ float tabs(float x) { return fabsf(x); }
 // x with its sign flipped when s is set (one XOR of the sign bit).
@@ -139,11 +148,15 @@ __device__ __forceinline__ float flip(float x, uint32_t s)
 // -F to node j.  Staged record: rho, u[0..2], rho E, rho phi, c (the
 // momentum is rebuilt as rho u, the pressure as rho c^2 / gamma: seven values
 // per node keep three FP64 owner workgroups within one CU's LDS).
+// Where a product is rounded and where it goes unrounded into a sum is written
+// out here: left to the compiler it differed from kernel to kernel (the pressure
+// sum), and with it the last bit of an FP32 flux.
 struct OpFlux {
     static constexpr int NIN = 6, NS = 7, NOUT = 6, NW = 3, NWOUT = 0, MODE = ANTI;
     template <typename T>
     __device__ static __forceinline__ void stage(const T *x, T *s, T gamma)
     {
+#pragma clang fp contract(off)
         const T ir = trcp(x[0]);
         s[0] = x[0];
         s[1] = x[1] * ir;
@@ -151,28 +164,30 @@ struct OpFlux {
         s[3] = x[3] * ir;
         s[4] = x[4];
         s[5] = x[5];
-        const T p = (gamma - T(1)) * (x[4] - T(0.5) * (x[1] * s[1] + x[2] * s[2] + x[3] * s[3]));
+        const T p = (gamma - T(1)) * tfma(T(-0.5), dot3(x + 1, s + 1), x[4]);
         s[6] = tsqrt(gamma * p * ir);
     }
     template <typename T>
     __device__ static __forceinline__ void edge(const T *a, const T *b, const T *n, T gamma,
                                                 double *yi, double *, double *)
     {
+#pragma clang fp contract(off)
         const T h = T(0.5);
-        const T Ua = a[1] * n[0] + a[2] * n[1] + a[3] * n[2];
-        const T Ub = b[1] * n[0] + b[2] * n[1] + b[3] * n[2];
-        const T nn = tsqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
-        const T hl = h * (tabs(h * (Ua + Ub)) + h * (a[6] + b[6]) * nn);
+        const T Ua = dot3(a + 1, n), Ub = dot3(b + 1, n);
+        const T nn = tsqrt(dot3(n, n));
+        const T hl = h * tfma(h * (a[6] + b[6]), nn, tabs(h * (Ua + Ub)));
         const T ma = a[0] * Ua, mb = b[0] * Ub;  // mass fluxes
         const T ig = T(1) / gamma;
-        const T pa = a[0] * a[6] * a[6] * ig, pb = b[0] * b[6] * b[6] * ig;
-        const T pp = pa + pb;
-        yi[0] = (double)(h * (ma + mb) - hl * (b[0] - a[0]));
-        yi[1] = (double)(h * (ma * a[1] + mb * b[1] + pp * n[0]) - hl * (b[0] * b[1] - a[0] * a[1]));
-        yi[2] = (double)(h * (ma * a[2] + mb * b[2] + pp * n[1]) - hl * (b[0] * b[2] - a[0] * a[2]));
-        yi[3] = (double)(h * (ma * a[3] + mb * b[3] + pp * n[2]) - hl * (b[0] * b[3] - a[0] * a[3]));
-        yi[4] = (double)(h * ((a[4] + pa) * Ua + (b[4] + pb) * Ub) - hl * (b[4] - a[4]));
-        yi[5] = (double)(h * (a[5] * Ua + b[5] * Ub) - hl * (b[5] - a[5]));
+        const T ka = a[0] * a[6] * a[6], kb = b[0] * b[6] * b[6];  // gamma p
+        const T pp = tfma(ka, ig, kb * ig);
+        // h s - hl d
+        auto out = [&](T s, T d) { return (double)tfma(h, s, -(hl * d)); };
+        yi[0] = out(tfma(a[0], Ua, mb), b[0] - a[0]);
+#pragma unroll
+        for (int k = 1; k < 4; ++k)  // ma a_k + mb b_k + pp n, rho b_k - rho a_k
+            yi[k] = out(tfma(pp, n[k - 1], tfma(ma, a[k], mb * b[k])), tfma(b[0], b[k], -(a[0] * a[k])));
+        yi[4] = out(tfma(tfma(ka, ig, a[4]), Ua, tfma(kb, ig, b[4]) * Ub), b[4] - a[4]);
+        yi[5] = out(tfma(a[5], Ua, b[5] * Ub), b[5] - a[5]);
     }
 };
 
@@ -183,22 +198,23 @@ struct OpSpecrad {
     template <typename T>
     __device__ static __forceinline__ void stage(const T *x, T *s, T gamma)
     {
+#pragma clang fp contract(off)
         const T ir = trcp(x[0]);
         s[0] = x[1] * ir;
         s[1] = x[2] * ir;
         s[2] = x[3] * ir;
-        const T p = (gamma - T(1)) * (x[4] - T(0.5) * (x[1] * s[0] + x[2] * s[1] + x[3] * s[2]));
+        const T p = (gamma - T(1)) * tfma(T(-0.5), dot3(x + 1, s), x[4]);
         s[3] = tsqrt(gamma * p * ir);
     }
     template <typename T>
     __device__ static __forceinline__ void edge(const T *a, const T *b, const T *n, T,
                                                 double *yi, double *, double *)
     {
+#pragma clang fp contract(off)
         const T h = T(0.5);
-        const T Ua = a[0] * n[0] + a[1] * n[1] + a[2] * n[2];
-        const T Ub = b[0] * n[0] + b[1] * n[1] + b[2] * n[2];
-        const T nn = tsqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
-        yi[0] = (double)(tabs(h * (Ua + Ub)) + h * (a[3] + b[3]) * nn);
+        const T Ua = dot3(a, n), Ub = dot3(b, n);
+        const T nn = tsqrt(dot3(n, n));
+        yi[0] = (double)tfma(h * (a[3] + b[3]), nn, tabs(h * (Ua + Ub)));
     }
 };
 
@@ -1148,6 +1164,26 @@ struct Message<OpGrad> {
     }
 };
 
+// Whether a visit has to evaluate its edge the way round that the edge's other
+// evaluations take: F(a, b, w) = -F(b, a, -w) does not hold to the bit in FP32
+// (an FMA rounds one end's product and not the other's), and the results are FP64
+// sums that show it.  The spectral radius is symmetric to the bit, and in FP64
+// the difference is no larger than the sums' own rounding.
+template <typename T, class Op>
+constexpr bool one_way() { return sizeof(T) == 4 && Op::MODE == ANTI; }
+
+// The records of the owned and the far end as the edge's first and second; with
+// last the owned end is the second.
+template <int NS, typename T>
+__device__ __forceinline__ void in_order(const T *own, const T *far, uint32_t last, T *a, T *b)
+{
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        a[i] = last ? far[i] : own[i];
+        b[i] = last ? own[i] : far[i];
+    }
+}
+
 // WAVES: waves per SIMD the registers must allow (three workgroups per CU where
 // the LDS holds three: the FP64 flux stage of a 1M-node RCM mesh takes 190 us
 // with 24 wavefronts per CU, 225 us with 16).  AHEAD: entries of a node's list
@@ -1203,6 +1239,9 @@ __device__ __forceinline__ double stage_one(const StagePtrs<T> &sp, int v, int g
 // barriers, and its wavefronts wait 80 % of their time (LDS pipe 30 % busy).
 // The owner kernel's atomics need no rounds and take 110 us on that mesh, but
 // their order varies.
+// An FP32 cut edge is evaluated its first node first in both its clusters (the two
+// records are exchanged where the owned end is the second), so that its two
+// increments cancel to the bit.
 template <typename T, class Op, int KC, bool STAGE = false>
 __global__ __launch_bounds__(kOwnerThreads, (FixedTune<T, Op>::WAVES)) void k_edge_fixed(
     OwnerPtrs p, FixedPtrs f, Arrays<T> a, T gamma, int N, int Kr, int ncl, int remap, int overwrite,
@@ -1261,15 +1300,24 @@ __global__ __launch_bounds__(kOwnerThreads, (FixedTune<T, Op>::WAVES)) void k_ed
             const int s = s0 + k - ib.y;
             const int eid = ld(p.cv_eid, s), oth = ld(p.cv_oth, s), own = (int)ld(p.cv_own, s);
             const uint32_t second = (uint32_t)oth >> 31;
+            const uint32_t last = one_way<T, Op>() ? second : 0u, turned = second ^ last;
 #pragma unroll
-            for (int d = 0; d < Op::NW; ++d) w[d] = flip(ld(a.w[d], eid), second);
+            for (int d = 0; d < Op::NW; ++d) w[d] = flip(ld(a.w[d], eid), turned);
             load_stage<Op>(a, oth & 0x7fffffff, gamma, sb);
             lds_get<T, Op::NS>(ss, K, own, sa);
-            M::type::edge(sa, sb, w, gamma, m, m2, wo);
+            if constexpr (one_way<T, Op>()) {
+                T s1[Op::NS], s2[Op::NS];
+                in_order<Op::NS>(sa, sb, last, s1, s2);
+                M::type::edge(s1, s2, w, gamma, m, m2, wo);
+#pragma unroll
+                for (int i = 0; i < M::NM; ++i) m[i] = flip(m[i], last);
+            } else {
+                M::type::edge(sa, sb, w, gamma, m, m2, wo);
+            }
             if constexpr (Op::NWOUT > 0) {
                 if (v0 + own < (oth & 0x7fffffff)) {  // written once, from the smaller end
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) st(a.wo[d], eid, flip(wo[d], second));
+                    for (int d = 0; d < 3; ++d) st(a.wo[d], eid, flip(wo[d], turned));
                 }
             }
         }
@@ -1323,6 +1371,10 @@ __global__ __launch_bounds__(kOwnerThreads, (FixedTune<T, Op>::WAVES)) void k_ed
 // trips to memory (offsets, visits, records) and one barrier: 5.8 us per FP64
 // stage at 8,000 nodes, 250 workgroups on 256 CUs, where staged records and entry
 // lists took 6.6 and sixteen 512-node clusters 13.5.
+// An FP32 edge is evaluated its first node first for both ends (one_way).  turn: an
+// edge between two owner clusters from its owned end, as the owner loop over the
+// clusters does, so that a mesh's FP32 results don't depend on which of the two
+// loops runs it.
 struct FinePtrs {
     const int *off, *eid, *oth;
     const uint16_t *own;
@@ -1332,7 +1384,7 @@ struct FinePtrs {
 template <typename T, class Op, bool STAGE = false>
 __global__ __launch_bounds__(kOwnerThreads) void k_edge_fine(FinePtrs f, Arrays<T> a, T gamma, int N,
                                                              int nch, int remap, int overwrite,
-                                                             StagePtrs<T> sp = {})
+                                                             int turn, StagePtrs<T> sp = {})
 {
     constexpr int NT = kOwnerThreads, K = kFixedFine;
     using M = Message<Op>;
@@ -1370,26 +1422,39 @@ __global__ __launch_bounds__(kOwnerThreads) void k_edge_fine(FinePtrs f, Arrays<
     for (int b = 0; b < n; b += NT) {
         const int k = b + t;
         if (k < n) {
-            const int eid = ld(f.eid, s0 + k), oth = ld(f.oth, s0 + k), own = v0 + (int)ld(f.own, s0 + k);
+            const int eid = ld(f.eid, s0 + k), oth = ld(f.oth, s0 + k), of = (int)ld(f.own, s0 + k);
+            const int own = v0 + (of & 0x7fff), far = oth & 0x7fffffff;
+            // an edge's second end stands first when it is the owned one, unless the
+            // edge is to be evaluated one way only (turn: where it lies in one cluster)
             const uint32_t second = (uint32_t)oth >> 31;
+            const uint32_t last = one_way<T, Op>() ? second & (turn ? (uint32_t)of >> 15 : 1u) : 0u;
+            const uint32_t turned = second ^ last;
             T w[Op::NW], xa[Op::NIN], xb[Op::NIN], sa[Op::NS], sb[Op::NS];
 #pragma unroll
             for (int d = 0; d < Op::NW; ++d) w[d] = ld(a.w[d], eid);
 #pragma unroll
             for (int v = 0; v < Op::NIN; ++v) {
                 xa[v] = ld(a.x[v], own);
-                xb[v] = ld(a.x[v], oth & 0x7fffffff);
+                xb[v] = ld(a.x[v], far);
             }
             Op::stage(xa, sa, gamma);
             Op::stage(xb, sb, gamma);
 #pragma unroll
-            for (int d = 0; d < Op::NW; ++d) w[d] = flip(w[d], second);
+            for (int d = 0; d < Op::NW; ++d) w[d] = flip(w[d], turned);
             double m[M::NM], m2[M::NM], wo[3] = {0.0, 0.0, 0.0};
-            M::type::edge(sa, sb, w, gamma, m, m2, wo);
-            if constexpr (Op::NWOUT > 0) {
-                if (own < (oth & 0x7fffffff)) {  // written once, from the smaller end
+            if constexpr (one_way<T, Op>()) {
+                T s1[Op::NS], s2[Op::NS];
+                in_order<Op::NS>(sa, sb, last, s1, s2);
+                M::type::edge(s1, s2, w, gamma, m, m2, wo);
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) st(a.wo[d], eid, flip(wo[d], second));
+                for (int i = 0; i < M::NM; ++i) m[i] = flip(m[i], last);
+            } else {
+                M::type::edge(sa, sb, w, gamma, m, m2, wo);
+            }
+            if constexpr (Op::NWOUT > 0) {
+                if (own < far) {  // written once, from the smaller end
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) st(a.wo[d], eid, flip(wo[d], turned));
                 }
             }
 #pragma unroll
@@ -1819,7 +1884,7 @@ int run_fixed(const DevPlan &P, const EdgeArrays &a, double gamma, hipStream_t s
         const FinePtrs fp{X.cv_off, X.cv_eid, X.cv_oth, X.cv_own, X.node_off};
         hipLaunchKernelGGL((k_edge_fine<T, Op, STAGE>), dim3(X.nchunk), dim3(kOwnerThreads),
                            fine_lds<Op>(), st, fp, typed<T>(a), (T)gamma, P.N, X.nchunk, lo.xcd_remap,
-                           lo.overwrite, sp);
+                           lo.overwrite, lo.turn, sp);
         return (int)hipGetLastError();
     }
     const OwnerPtrs op{X.iblk, X.iw, X.cv_off, X.cv_eid, X.cv_oth, X.cv_own};

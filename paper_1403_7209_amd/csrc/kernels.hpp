@@ -35,7 +35,8 @@ __device__ __forceinline__ int xcd_map(int k, int n)
 // below the high half of off[r K + k]: the visit's slot in the round, bit 15 set
 // when the node is the second end of an interior edge.  k_edge_fine (fine) runs
 // the chunk's (edge, end) pairs cv_off[c] .. cv_off[c+1], which are sorted by
-// owned node: node i's are node_off[i] .. node_off[i+1].
+// owned node: node i's are node_off[i] .. node_off[i+1]; bit 15 of cv_own is then
+// set for an edge of its owner cluster's interior block.
 struct FixedPlan {
     int K = 0, nchunk = 0;  // K = 0: no lists
     bool fine = false;      // chunks smaller than the owner clusters
@@ -116,6 +117,7 @@ struct LaunchOpts {
     int xcd_remap = 1;  // give each XCD a contiguous range of partitions/clusters
     int overwrite = 0;  // owner variant: res = sum instead of res += sum
     int fixed = 0;      // coloured and owner variants: through the plan's fixed-order lists
+    int turn = 0;       // fixed: edges between owner clusters from the owned end (see k_edge_fine)
 };
 
 // Returns 0 or a hipError_t value.

@@ -661,6 +661,7 @@ int edge_loop(opf_ctx *ctx, int kernel, opf_set s, int nargs, const opf_arg *arg
         if (takes_fixed(pr, variant)) {
             const size_t fl = opf::gpu::fixed_lds_bytes(op, fp32, pr.dev.fixed);
             lo.fixed = fl <= ctx->max_lds ? 1 : 0;
+            lo.turn = variant == OPF_V_OWNER;
             if (lo.fixed) lds = fl;
         }
         if (lds > ctx->lds_limit) {
@@ -2006,6 +2007,7 @@ int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat
         return ctx->fail(OPF_EINVAL, "a workgroup needs " + std::to_string(lds) + " B of LDS");
     opf::gpu::LaunchOpts lo;
     lo.fixed = takes_fixed(pr, how.variant) ? 1 : 0;
+    lo.turn = how.variant == OPF_V_OWNER;
     if (lo.fixed) lds = opf::gpu::fixed_lds_bytes(opf::gpu::OP_FLUX, fp32, pr.dev.fixed);
     if (lds > ctx->lds_limit) {
         int e = opf::gpu::set_lds_limit(ctx->max_lds);

@@ -954,13 +954,16 @@ void build_fixed(const Plan &P, int K, int NT, FixedLists &F)
         F.cv_eid.resize(2 * P.E);
         F.cv_oth.resize(2 * P.E);
         F.cv_own.resize(2 * P.E);
+        std::vector<uint16_t> interior(P.E, 0);
+        for (int64_t c = 0; c < P.nclusters(); ++c)
+            std::fill_n(interior.begin() + P.cl_prim[2 * c], P.cl_nint[c], (uint16_t)0x8000);
         for (int64_t e = 0; e < P.E; ++e)
             for (int h = 0; h < 2; ++h) {
                 const int32_t v = P.e2n[2 * e + h];
                 const int64_t s = at[v]++;
                 F.cv_eid[s] = (int32_t)e;
                 F.cv_oth[s] = (int32_t)((uint32_t)P.e2n[2 * e + 1 - h] | ((uint32_t)h << 31));
-                F.cv_own[s] = (uint16_t)(v % K);
+                F.cv_own[s] = (uint16_t)((v % K) | interior[e]);
             }
         // at[v] is now past node v's last visit
         F.node_off.assign(P.N + 1, 0);

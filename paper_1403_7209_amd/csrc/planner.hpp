@@ -126,7 +126,8 @@ struct FixedLists {
     bool fine = false;  // chunks smaller than the owner clusters, visits of their own, no rounds
     std::vector<int32_t> iblk;               // [2 nchunk] (first edge, count)
     std::vector<int32_t> cv_off, cv_eid, cv_oth;  // fine: every (edge, end) pair by owned node
-    std::vector<uint16_t> cv_own;
+    std::vector<uint16_t> cv_own;   // the owned end in its chunk, bit 15: the edge is in its
+                                    // owner cluster's interior block
     std::vector<int32_t> node_off;  // fine: [N+1] each node's visits
     std::vector<int32_t> rnd_off;   // [nchunk+1] rounds of each chunk
     std::vector<int32_t> ent_base;  // [rounds+1] first entry of each round
