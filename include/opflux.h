@@ -112,8 +112,9 @@ typedef enum {
                            clusters run twice) and writes its nodes' totals
                            once; single launch, no colours (owner-compute as in
                            Sec. 3.2, at workgroup level).  LDS accumulation uses
-                           FP64 LDS atomics, so the summation order varies
-                           (on meshes of up to 24,576 nodes it is fixed)        */
+                           FP64 LDS atomics, so the summation order varies.
+                           A plan of 2 to 48 clusters of at most 512 nodes runs
+                           over smaller chunks instead, in a fixed order          */
     OPF_V_COLOURED_LDS_ATOMIC = 3, /* as COLOURED, with LDS atomics in place
                            of the edge colours inside a partition               */
     OPF_V_FLAT = 4      /* one level of colours over the whole edge set (no

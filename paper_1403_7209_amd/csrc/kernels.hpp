@@ -52,10 +52,10 @@ struct FixedPlan {
 // The largest chunk of the fixed-order loop: one node per thread.
 constexpr int kFixedMaxK = kOwnerThreads;
 // The chunk of a small mesh, the most nodes of one (see fixed_chunk), and the
-// most for which the owner variant takes it (see takes_fixed).
+// most owner clusters for which the owner variant takes it (see takes_fixed).
 constexpr int kFixedFine = 32;
 constexpr int kFixedFineNodes = 98304;
-constexpr int kFixedFineOwner = 24576;
+constexpr int kFixedFineOwner = 48;
 // Stages of one iteration.
 constexpr int kStages = 5;
 

@@ -523,16 +523,19 @@ int check_gbl_disjoint(opf_ctx *ctx, const void *p, size_t bytes, std::initializ
 
 // Whether a loop of this variant runs over the plan's fixed-order lists: the
 // coloured variant wherever there are any (the same fixed order on every run,
-// without a launch per partition colour); the owner variant up to 24,576 nodes,
-// where its few clusters take as long as one of them does: flux and adjoint at
-// 8,000 nodes 5.5 and 7.5 us against 11.2 and 14.4 over the clusters, at 21,952
+// without a launch per partition colour); the owner variant up to 48 clusters,
+// which take as long as one of them does: flux and adjoint with 512-node clusters
+// at 8,000 nodes 5.5 and 7.5 us against 11.2 and 14.4 over the clusters, at 21,952
 // 8.8 and 12.7 against 11.7 and 15.4, at 46,656 14.2 and 21.9 against 12.2 and
-// 16.4.
+// 16.4.  Smaller clusters take less time each: adjoint and second-order flux at
+// 21,952 nodes 10.7 and 17.3 us against 7.8 and 12.1 over 64-node clusters, 11.5
+// and 17.5 against 11.4 and 14.2 over 256-node ones; at 12,167 nodes 8.2 and 11.5
+// against 6.7 and 9.3 over 64-node ones.
 bool takes_fixed(const PlanRec &pr, int variant)
 {
     const opf::gpu::FixedPlan &X = pr.dev.fixed;
     if (variant == OPF_V_COLOURED) return X.K > 0;
-    return variant == OPF_V_OWNER && X.fine && pr.dev.N <= opf::gpu::kFixedFineOwner;
+    return variant == OPF_V_OWNER && X.fine && pr.dev.ncl <= opf::gpu::kFixedFineOwner;
 }
 
 int edge_loop(opf_ctx *ctx, int kernel, opf_set s, int nargs, const opf_arg *args, int ngbl,
