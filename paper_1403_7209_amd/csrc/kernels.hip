@@ -79,7 +79,9 @@ static __device__ __align__(256) double scratch[opf::gpu::kSumTail + 6 * opf::gp
 #endif
 // The second-order loop holds 30 values per node in LDS: one workgroup per CU,
 // so its workgroups take more threads (1024 with one edge each: 2.1M nodes 373
-// us, 768 with two: 382, 512 with one: 400).  The
+// us, 768 with two: 382, 512 with one: 400).  Clusters of other sizes than 512
+// take 768: 1M nodes, 64-, 128- and 256-node clusters 405, 283 and 231 us, with
+// 1024 441, 301 and 237 (their instance spills registers there).  The
 // gradient runs in halves of 12 values per node, three 512-thread workgroups
 // per CU.
 #ifndef OPF_GRAD_BATCH
@@ -408,7 +410,8 @@ struct OpFlux2 {
 };
 
 // B: edges each thread resolves before computing in the interior loop, BC in
-// the cut-visit loop (whose gathered records cost registers).
+// the cut-visit loop (whose gathered records cost registers); NT: threads.  B0 and
+// NT0: for the cluster sizes without an instance of their own.
 // ORDER: the plan's order of the cut visits.  FOREIGN (by foreign node): the
 // lanes of a wavefront share foreign records, which pays where those are wide
 // (second order, 25 values: 373 us against 392 in edge order at 2.1M nodes; the
@@ -430,7 +433,7 @@ enum CutOrder { SPREAD, FOREIGN, EDGE };
 
 template <typename T, class Op>
 struct OwnerTune {
-    static constexpr int B = 2, BC = 2, WAVES = 0, NT = kOwnerThreads;
+    static constexpr int B = 2, BC = 2, WAVES = 0, NT = kOwnerThreads, B0 = B, NT0 = NT;
     static constexpr bool EARLY = false;
     static constexpr CutOrder ORDER = SPREAD;
     static constexpr bool STREAM = false;
@@ -438,7 +441,7 @@ struct OwnerTune {
 template <>
 struct OwnerTune<float, OpFlux> {
     static constexpr int B = OPF_FLUX32_BATCH, BC = OPF_FLUX32_CUT_BATCH, WAVES = OPF_FLUX32_WAVES,
-                         NT = kOwnerThreads;
+                         NT = kOwnerThreads, B0 = B, NT0 = NT;
     static constexpr bool EARLY = false;
     static constexpr CutOrder ORDER = SPREAD;
     static constexpr bool STREAM = true;
@@ -446,7 +449,7 @@ struct OwnerTune<float, OpFlux> {
 template <>
 struct OwnerTune<double, OpFlux> {
     static constexpr int B = OPF_FLUX64_BATCH, BC = OPF_FLUX64_CUT_BATCH, WAVES = OPF_FLUX64_WAVES,
-                         NT = kOwnerThreads;
+                         NT = kOwnerThreads, B0 = B, NT0 = NT;
     static constexpr bool EARLY = true;
     static constexpr CutOrder ORDER = EDGE;
     static constexpr bool STREAM = true;
@@ -454,14 +457,15 @@ struct OwnerTune<double, OpFlux> {
 template <>
 struct OwnerTune<double, OpAdjoint> {
     static constexpr int B = OPF_ADJ_BATCH, BC = OPF_ADJ_CUT_BATCH, WAVES = OPF_ADJ_WAVES,
-                         NT = kOwnerThreads;
+                         NT = kOwnerThreads, B0 = B, NT0 = NT;
     static constexpr bool EARLY = false;
     static constexpr CutOrder ORDER = FOREIGN;
     static constexpr bool STREAM = false;
 };
 template <>
 struct OwnerTune<double, OpGradH> {
-    static constexpr int B = OPF_GRAD_BATCH, BC = OPF_GRAD_BATCH, WAVES = 0, NT = OPF_GRAD_THREADS;
+    static constexpr int B = OPF_GRAD_BATCH, BC = OPF_GRAD_BATCH, WAVES = 0, NT = OPF_GRAD_THREADS, B0 = B,
+                         NT0 = NT;
     static constexpr bool EARLY = false;
     static constexpr CutOrder ORDER = SPREAD;
     static constexpr bool STREAM = false;
@@ -481,7 +485,7 @@ struct OwnerOp<OpGrad> {
 template <>
 struct OwnerTune<double, OpFlux2> {
     static constexpr int B = OPF_FLUX2_BATCH, BC = OPF_FLUX2_CUT_BATCH, WAVES = 0,
-                         NT = OPF_FLUX2_THREADS;
+                         NT = OPF_FLUX2_THREADS, B0 = 2, NT0 = 768;
     static constexpr bool EARLY = false;
     static constexpr CutOrder ORDER = FOREIGN;
     static constexpr bool STREAM = false;
@@ -937,7 +941,7 @@ __global__ __launch_bounds__(NT, (owner_waves<T, Op, NT>())) void k_edge_owner(
     OwnerPtrs p, Arrays<T> a0, T gamma, int N, int Kr, int ncl, int remap, int overwrite,
     StagePtrs<T> sp = {})
 {
-    constexpr int B = OwnerTune<T, Op>::B;
+    constexpr int B = KC > 0 ? OwnerTune<T, Op>::B : OwnerTune<T, Op>::B0;
     constexpr bool S = HINT && OwnerTune<T, Op>::STREAM;
     const int K = KC > 0 ? KC : Kr;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1841,8 +1845,8 @@ void launch_owner(bool hint, int grid, size_t lds, hipStream_t st, const OwnerPt
         launch_owner_kc<T, O, NT, kOwnerKC, STAGE, H>(hint, grid, lds, st, op, a, gamma, P, lo,
                                                       overwrite, sp);
     else
-        launch_owner_kc<T, O, NT, 0, STAGE, H>(hint, grid, lds, st, op, a, gamma, P, lo, overwrite,
-                                               sp);
+        launch_owner_kc<T, O, OwnerTune<T, O>::NT0, 0, STAGE, H>(hint, grid, lds, st, op, a, gamma, P,
+                                                                 lo, overwrite, sp);
 }
 
 template <typename T, class Op>
@@ -1984,7 +1988,8 @@ int raise_coloured(size_t bytes)
 template <typename T, class O, int NT, bool STAGE, bool H>
 int raise_owner(size_t bytes)
 {
-    int rc = raise_one(reinterpret_cast<const void *>(&k_edge_owner<T, O, NT, 0, STAGE, H, false>), bytes);
+    constexpr int NT0 = OwnerTune<T, O>::NT0;
+    int rc = raise_one(reinterpret_cast<const void *>(&k_edge_owner<T, O, NT0, 0, STAGE, H, false>), bytes);
     if (!rc)
         rc = raise_one(reinterpret_cast<const void *>(&k_edge_owner<T, O, NT, kOwnerKC, STAGE, H, false>),
                        bytes);
@@ -2002,7 +2007,7 @@ int raise_owner(size_t bytes)
     }
     if constexpr (OwnerTune<T, O>::STREAM) {
         if (!rc)
-            rc = raise_one(reinterpret_cast<const void *>(&k_edge_owner<T, O, NT, 0, STAGE, H, true>),
+            rc = raise_one(reinterpret_cast<const void *>(&k_edge_owner<T, O, NT0, 0, STAGE, H, true>),
                            bytes);
         if (!rc)
             rc = raise_one(
