@@ -422,7 +422,9 @@ struct OpFlux2 {
 // ends of 16 visits in distinct LDS banks): the FP32 flux and the gradient, bound
 // by their LDS updates (edge order costs the FP32 flux 2 %).
 // EARLY: the next round's cut visits are read while this one's records are
-// gathered.  The FP64 flux gains (2.1M nodes 1 %, a share of 184,857 nodes 3 %);
+// gathered.  The FP64 flux gains (2.1M nodes 1 %, a share of 184,857 nodes 3 %),
+// except, without the stage, over clusters of other sizes than 512 (1M nodes,
+// 64-node clusters 122 us without it, 131 with; the stage 1018 and 991 for five);
 // the adjoint, at its limit of registers, loses 2.5 % and the others up to 0.5 %.
 // STREAM: non-temporal hints on the loop's once-touched data (ld1/st1) when
 // its arrays exceed the last-level cache (owner_streams).  They pay in the
@@ -1038,7 +1040,7 @@ __global__ __launch_bounds__(NT, (owner_waves<T, Op, NT>())) void k_edge_owner(
             }
         }
     };
-    constexpr bool EARLY = OwnerTune<T, Op>::EARLY;
+    constexpr bool EARLY = OwnerTune<T, Op>::EARLY && (STAGE || KC > 0);
     if constexpr (EARLY) visits(threadIdx.x);
     for (int k0 = threadIdx.x; k0 < ns; k0 += NT * BC) {
         if constexpr (!EARLY) visits(k0);
