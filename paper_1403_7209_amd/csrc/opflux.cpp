@@ -1942,14 +1942,11 @@ int stage_rows(const PlanRec &pr, int variant)
     return takes_fixed(pr, variant) ? pr.dev.fixed.nchunk : pr.dev.ncl;
 }
 
-// The fused edge loop + stage.
-int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat n, opf_dat q0,
-                    opf_dat vol, opf_dat dt, opf_dat qout, double gamma, double alpha,
-                    double *ss_dev, void *stream, const StageHow &how)
+// The checks of a fused stage that need no device: its arguments, and the plan of
+// the edge map (returned in `plan`).
+int check_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat n, opf_dat q0,
+                opf_dat vol, opf_dat dt, opf_dat qout, opf_dat res, const double *ss_dev, PlanRec *&plan)
 {
-    if (!ctx) return OPF_EINVAL;
-    const bool noalloc = how.noalloc;
-    ctx->err.clear();
     if (!ctx->set_ok(edges) || !ctx->map_ok(e2n)) return ctx->fail(OPF_EINVAL, "invalid handle");
     const MapRec &mr = ctx->maps[e2n];
     if (mr.dim != 2 || mr.from != edges)
@@ -1972,17 +1969,17 @@ int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat
         rc = check_arg(ctx, a[k], w[k], k);
     }
     if (rc) return rc;
-    if (how.res >= 0) {
-        const opf_arg ra = {how.res, 0, e2n, 6, OPF_F64, OPF_INC};
+    if (res >= 0) {
+        const opf_arg ra = {res, 0, e2n, 6, OPF_F64, OPF_INC};
         rc = check_arg(ctx, ra, Want{nodes, 0, e2n, 6, OPF_F64, OPF_INC}, 7);
         if (rc) return rc;
     }
     if (qout == q || qout == q0) return ctx->fail(OPF_EINVAL, "qout must not alias q or q0");
     if (!ss_dev) return ctx->fail(OPF_EINVAL, "ss must be device memory");
-    rc = check_disjoint(ctx, qout, {q, n, q0, vol, dt, how.res}, "fused stage qout");
-    if (!rc && how.res >= 0) rc = check_disjoint(ctx, how.res, {q, n, q0, vol, dt}, "fused stage res");
+    rc = check_disjoint(ctx, qout, {q, n, q0, vol, dt, res}, "fused stage qout");
+    if (!rc && res >= 0) rc = check_disjoint(ctx, res, {q, n, q0, vol, dt}, "fused stage res");
     if (!rc)
-        rc = check_gbl_disjoint(ctx, ss_dev, 6 * sizeof(double), {q, n, q0, vol, dt, qout, how.res},
+        rc = check_gbl_disjoint(ctx, ss_dev, 6 * sizeof(double), {q, n, q0, vol, dt, qout, res},
                                 "fused stage ss");
     if (rc) return rc;
     auto it = ctx->plans.find(e2n);
@@ -1990,6 +1987,17 @@ int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat
     PlanRec &pr = *it->second;
     if (pr.map_version != mr.version) return ctx->fail(OPF_ESTATE, "plan is stale: map re-declared");
     if (!pr.host.owner_ok) return ctx->fail(OPF_EINVAL, "the fused loop needs owner clusters");
+    plan = &pr;
+    return OPF_OK;
+}
+
+// Launches a stage that check_stage has passed.
+int launch_stage(opf_ctx *ctx, PlanRec &pr, opf_dat q, opf_dat n, opf_dat q0, opf_dat vol, opf_dat dt,
+                 opf_dat qout, double gamma, double alpha, double *ss_dev, void *stream,
+                 const StageHow &how)
+{
+    const bool noalloc = how.noalloc;
+    int rc = OPF_OK;
     double *partial = pr.dev.stage_partial;
     if (noalloc) {
         rc = device_bind(ctx);
@@ -2004,7 +2012,7 @@ int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat
         if (rc) return rc;
     }
     if (!pr.on_device) return ctx->fail(OPF_ESTATE, "plan is not on the device");
-    const bool fp32 = T == OPF_F32;
+    const bool fp32 = ctx->dats[q].type == OPF_F32;
     size_t lds = opf::gpu::edge_lds_bytes(opf::gpu::OP_FLUX, fp32, how.variant, pr.dev.umax, pr.dev.K);
     if (lds > ctx->max_lds)
         return ctx->fail(OPF_EINVAL, "a workgroup needs " + std::to_string(lds) + " B of LDS");
@@ -2048,6 +2056,19 @@ int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat
     return noalloc ? OPF_OK : scratch_end(ctx, st);
 }
 
+// The fused edge loop + stage.
+int edge_flux_stage(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_dat n, opf_dat q0,
+                    opf_dat vol, opf_dat dt, opf_dat qout, double gamma, double alpha,
+                    double *ss_dev, void *stream, const StageHow &how)
+{
+    if (!ctx) return OPF_EINVAL;
+    ctx->err.clear();
+    PlanRec *pr = nullptr;
+    const int rc = check_stage(ctx, edges, e2n, q, n, q0, vol, dt, qout, how.res, ss_dev, pr);
+    if (rc) return rc;
+    return launch_stage(ctx, *pr, q, n, q0, vol, dt, qout, gamma, alpha, ss_dev, stream, how);
+}
+
 }  // namespace
 
 extern "C" {
@@ -2088,12 +2109,15 @@ int opf_rk_iteration(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_da
     int rc = check_gbl_disjoint(ctx, ss_dev, 6 * S * sizeof(double), {q, n, vol, dt, qb, qc, res},
                                 "iteration ss");
     if (!rc) rc = check_disjoint(ctx, qc, {q, qb, n, vol, dt, res}, "iteration qc");
+    // the three kinds of stage, all before the first is launched: from q, from qb
+    // into qc, from qc
+    PlanRec *pr = nullptr;
+    if (!rc) rc = check_stage(ctx, edges, e2n, q, n, q, vol, dt, qb, res, ss_dev, pr);
+    if (!rc) rc = check_stage(ctx, edges, e2n, qb, n, q, vol, dt, qc, -1, ss_dev, pr);
+    if (!rc) rc = check_stage(ctx, edges, e2n, qc, n, q, vol, dt, qb, -1, ss_dev, pr);
+    if (!rc) rc = device_ready(ctx);
     if (rc) return rc;
-    auto it = ctx->plans.find(e2n);
-    if (it == ctx->plans.end()) return ctx->fail(OPF_ESTATE, "no plan for this map: call opf_plan");
-    rc = device_ready(ctx);
-    if (rc) return rc;
-    if (variant == OPF_V_COLOURED && (!it->second->host.coloured_ok || !takes_fixed(*it->second, variant)))
+    if (variant == OPF_V_COLOURED && (!pr->host.coloured_ok || !takes_fixed(*pr, variant)))
         return ctx->fail(OPF_EINVAL, "the plan has no fixed-order lists (a two-level colouring and "
                                      "clusters of at most 512 nodes are needed)");
     const hipStream_t st = static_cast<hipStream_t>(stream);
@@ -2106,14 +2130,12 @@ int opf_rk_iteration(opf_ctx *ctx, opf_set edges, opf_map e2n, opf_dat q, opf_da
         const opf_dat dst = k % 2 ? qc : qb;
         how.set = k;
         how.res = k == 0 ? res : -1;
-        rc = edge_flux_stage(ctx, edges, e2n, src, n, q, vol, dt, dst, gamma, alpha[k], ss_dev + 6 * k,
-                             stream, how);
+        rc = launch_stage(ctx, *pr, src, n, q, vol, dt, dst, gamma, alpha[k], ss_dev + 6 * k, stream, how);
         src = dst;
     }
     if (!rc) {
-        const PlanRec &pr = *it->second;
-        const int e = opf::gpu::launch_sum_partials(stage_rows(pr, variant), S, pr.dev.stage_partial,
-                                                    pr.dev.stage_stride, ss_dev, true, st);
+        const int e = opf::gpu::launch_sum_partials(stage_rows(*pr, variant), S, pr->dev.stage_partial,
+                                                    pr->dev.stage_stride, ss_dev, true, st);
         if (e) rc = hip_fail(ctx, (hipError_t)e, "iteration launch");
     }
     const std::string why = ctx->err;
