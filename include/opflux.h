@@ -318,7 +318,7 @@ typedef struct {
  * two endpoints, in the segments and in the visit lists alike; (9) every edge
  * has exactly one flat colour and edges of one flat colour share no node.
  * Works without a GPU.  Errors: OPF_EPLAN (report filled),
- * OPF_ESTATE (no plan). */
+ * OPF_ESTATE (no plan), OPF_ENOMEM (not verified). */
 int opf_plan_verify(const opf_ctx *ctx, opf_map map, opf_plan_report *report);
 
 /* Declares a dat on set s borrowing device memory: dim components of type t,

@@ -122,6 +122,15 @@ struct opf_ctx {
         err = msg;
         return code;
     }
+    int no_memory(const char *msg) noexcept  // allocates nothing it can't do without
+    {
+        try {
+            err = msg;
+        } catch (const std::bad_alloc &) {
+            err.clear();
+        }
+        return OPF_ENOMEM;
+    }
     void *dalloc(size_t bytes)
     {
         if (bytes == 0) bytes = 256;
@@ -1315,55 +1324,56 @@ int tet_loop(opf_ctx *ctx, int kernel, opf_set s, int nargs, const opf_arg *args
     if (rc) return rc;
     if (!it->second->on_device) return ctx->fail(OPF_ESTATE, "plan is not on the device");
     opf::gpu::TetArrays ta;
-    if (gather) {
-        DevTetInverse *inv = nullptr;
-        try {
+    DevTetInverse *inv = nullptr;
+    try {
+        if (gather) {
             rc = tet_inverse(ctx, t2n, t2e, it->second->host, inv);
-        } catch (const std::bad_alloc &) {
-            free_tinv(ctx, ctx->tinv[std::make_pair((int)t2n, (int)t2e)]);
-            rc = ctx->fail(OPF_ENOMEM, "out of host memory building the tet incidence");
+        } else {
+            rc = device_map(ctx, t2n, ta.t2n);
+            if (!rc) rc = device_map(ctx, t2e, ta.t2e);
         }
-        if (!rc) {
-            ta.t2n = inv->t2n;
-            ta.t2e = inv->t2e;
-            ta.e2t_off = inv->e2t_off;
-            ta.e2t = inv->e2t;
-            ta.n2t_off = inv->n2t_off;
-            ta.n2t = inv->n2t;
-            ta.n2t_pos = inv->n2t_pos;
-            ta.scratch = inv->scratch;
-            ta.wT = inv->wT;
-            ta.ring_off = inv->ring_off;
-            ta.ring = inv->ring;
-            ta.chunk_e = reinterpret_cast<const int2 *>(inv->chunk_e);
-            ta.halo_off = inv->halo_off;
-            ta.halo = inv->halo;
-            ta.vsec_off = inv->vsec_off;
-            ta.vsec = inv->vsec;
-            ta.vloc_off = inv->vloc_off;
-            ta.vloc = inv->vloc;
-            ta.DV = inv->DV;
-            ta.edge_det = inv->edge_det;
-            ta.nchunk = inv->nchunk;
-            ta.KG = inv->KG;
-            ta.L = inv->L;
-            ta.RB = inv->RB;
-            ta.lk_node = inv->lk_node;
-            ta.lk_edge_off = inv->lk_edge_off;
-            ta.lk_edge = inv->lk_edge;
-            ta.lk_ends = inv->lk_ends;
-            ta.lk_halo_off = inv->lk_halo_off;
-            ta.lk_halo = inv->lk_halo;
-            ta.lk_ent_off = inv->lk_ent_off;
-            ta.lk_ent = inv->lk_ent;
-            ta.lk_chunks = inv->lk_chunks;
-            ta.lk_lds = inv->lk_lds;
-        }
-    } else {
-        rc = device_map(ctx, t2n, ta.t2n);
-        if (!rc) rc = device_map(ctx, t2e, ta.t2e);
+    } catch (const std::bad_alloc &) {
+        const auto half = ctx->tinv.find(std::make_pair((int)t2n, (int)t2e));
+        if (gather && half != ctx->tinv.end()) free_tinv(ctx, half->second);
+        return ctx->no_memory("out of host memory building the tet incidence");
     }
     if (rc) return rc;
+    if (gather) {
+        ta.t2n = inv->t2n;
+        ta.t2e = inv->t2e;
+        ta.e2t_off = inv->e2t_off;
+        ta.e2t = inv->e2t;
+        ta.n2t_off = inv->n2t_off;
+        ta.n2t = inv->n2t;
+        ta.n2t_pos = inv->n2t_pos;
+        ta.scratch = inv->scratch;
+        ta.wT = inv->wT;
+        ta.ring_off = inv->ring_off;
+        ta.ring = inv->ring;
+        ta.chunk_e = reinterpret_cast<const int2 *>(inv->chunk_e);
+        ta.halo_off = inv->halo_off;
+        ta.halo = inv->halo;
+        ta.vsec_off = inv->vsec_off;
+        ta.vsec = inv->vsec;
+        ta.vloc_off = inv->vloc_off;
+        ta.vloc = inv->vloc;
+        ta.DV = inv->DV;
+        ta.edge_det = inv->edge_det;
+        ta.nchunk = inv->nchunk;
+        ta.KG = inv->KG;
+        ta.L = inv->L;
+        ta.RB = inv->RB;
+        ta.lk_node = inv->lk_node;
+        ta.lk_edge_off = inv->lk_edge_off;
+        ta.lk_edge = inv->lk_edge;
+        ta.lk_ends = inv->lk_ends;
+        ta.lk_halo_off = inv->lk_halo_off;
+        ta.lk_halo = inv->lk_halo;
+        ta.lk_ent_off = inv->lk_ent_off;
+        ta.lk_ent = inv->lk_ent;
+        ta.lk_chunks = inv->lk_chunks;
+        ta.lk_lds = inv->lk_lds;
+    }
     ta.N = (int)ctx->sets[nodes].size;
     ta.E = (int)ctx->sets[edges].size;
     ta.e2n = it->second->dev.e2n;
@@ -1635,18 +1645,18 @@ int opf_plan(opf_ctx *ctx, opf_map map, const opf_plan_opts *opts, opf_plan_info
     }
     auto t0 = std::chrono::steady_clock::now();
     auto pr = std::unique_ptr<PlanRec>(new (std::nothrow) PlanRec());
-    if (!pr) return ctx->fail(OPF_ENOMEM, "out of host memory");
+    if (!pr) return ctx->no_memory("out of host memory");
     int rc;
     try {
         rc = opf::build_plan(ctx->sets[m.to].size, ctx->sets[m.from].size, m.idx.data(), po,
                              pr->host, ctx->err);
+        if (rc) return rc;
+        const opf::VerifyResult vr = opf::verify_plan(pr->host, m.idx.data());
+        if (!vr.ok)
+            return ctx->fail(OPF_EPLAN, "plan property " + std::to_string(vr.property) + ": " + vr.message);
     } catch (const std::bad_alloc &) {
-        return ctx->fail(OPF_ENOMEM, "out of host memory while planning");
+        return ctx->no_memory("out of host memory while planning");
     }
-    if (rc) return rc;
-    opf::VerifyResult vr = opf::verify_plan(pr->host, m.idx.data());
-    if (!vr.ok)
-        return ctx->fail(OPF_EPLAN, "plan property " + std::to_string(vr.property) + ": " + vr.message);
     pr->map_version = m.version;
     auto old = ctx->plans.find(map);
     if (old != ctx->plans.end() || !ctx->dmaps.empty() || !ctx->tinv.empty()) {
@@ -1670,15 +1680,22 @@ int opf_plan(opf_ctx *ctx, opf_map map, const opf_plan_opts *opts, opf_plan_info
             rc = upload_plan(ctx, *pr);
         } catch (const std::bad_alloc &) {
             free_plan(ctx, *pr);
-            rc = ctx->fail(OPF_ENOMEM, "out of host memory while planning");
+            rc = ctx->no_memory("out of host memory while planning");
         }
         if (rc) return rc;
+    }
+    const opf::Plan &P = pr->host;
+    const int64_t device_bytes = pr->device_bytes;
+    try {
+        ctx->plans[map] = std::move(pr);
+    } catch (const std::bad_alloc &) {
+        free_plan(ctx, *pr);
+        return ctx->no_memory("out of host memory while planning");
     }
     double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     ctx->sets[m.from].plan_map = map;
     ctx->sets[m.to].plan_map = map;
     if (info) {
-        const opf::Plan &P = pr->host;
         info->nblocks = P.nblocks();
         info->nblock_colours = P.nblock_colours;
         info->max_elem_colours = P.max_elem_colours;
@@ -1689,7 +1706,7 @@ int opf_plan(opf_ctx *ctx, opf_map map, const opf_plan_opts *opts, opf_plan_info
         info->bandwidth_before = P.bandwidth_before;
         info->bandwidth_after = P.bandwidth_after;
         info->plan_seconds = secs;
-        info->device_bytes = pr->device_bytes;
+        info->device_bytes = device_bytes;
         info->nclusters = P.nclusters();
         info->owner_edge_visits = P.owner_edge_visits;
         info->max_cluster_segments = P.max_cluster_segments;
@@ -1699,7 +1716,6 @@ int opf_plan(opf_ctx *ctx, opf_map map, const opf_plan_opts *opts, opf_plan_info
         info->flat_ok = P.flat_ok ? 1 : 0;
         info->coloured_ok = P.coloured_ok ? 1 : 0;
     }
-    ctx->plans[map] = std::move(pr);
     return OPF_OK;
 }
 
@@ -1776,7 +1792,12 @@ int opf_plan_verify(const opf_ctx *ctx, opf_map map, opf_plan_report *report)
     if (!ctx || !ctx->map_ok(map)) return OPF_EINVAL;
     auto it = ctx->plans.find(map);
     if (it == ctx->plans.end()) return OPF_ESTATE;
-    opf::VerifyResult vr = opf::verify_plan(it->second->host, ctx->maps[map].idx.data());
+    opf::VerifyResult vr;
+    try {
+        vr = opf::verify_plan(it->second->host, ctx->maps[map].idx.data());
+    } catch (const std::bad_alloc &) {
+        return OPF_ENOMEM;
+    }
     if (report) {
         report->ok = vr.ok ? 1 : 0;
         report->property = vr.property;

@@ -186,6 +186,7 @@ void parallel_for(int64_t n, const F &f)
     try {
         for (int64_t t = 1; t < nt; ++t) pool.emplace_back(work);
     } catch (const std::system_error &) {  // fewer threads then
+    } catch (const std::bad_alloc &) {
     }
     work();
     for (std::thread &th : pool) th.join();
