@@ -431,6 +431,8 @@ class Context:
                      variant=OWNER, stream=None):
         """Five fused stages from q with steps alpha (5 floats), the new state in qb; ss
         (5 x 6) = every stage's sum res^2.  variant OWNER, or COLOURED with res."""
+        if len(alpha) != 5:
+            raise ValueError("alpha must have 5 values")
         a = (ctypes.c_double * 5)(*alpha)
         self._check(self.lib.opf_rk_iteration(self._ctx, edges, e2n, q, n, vol, dt, qb, qc, res,
                                               gamma, a, self._gbl_ptr(ss, 30, "ss"), variant,

@@ -57,6 +57,14 @@ def test_shapes_and_types_without_a_device(name):
             assert call() == status
 
 
+@pytest.mark.parametrize("n", [0, 4, 6])
+def test_five_coefficients(n):
+    """Fewer used to be filled up with zeros."""
+    ctx = pk.Context(None)
+    with pytest.raises(ValueError):
+        ctx.rk_iteration(0, 0, 0, 0, 0, 0, 0, [0.1] * n, None)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("variant", [pk.OWNER, pk.COLOURED])
 def test_nothing_is_launched_for_a_bad_second_buffer(variant):
