@@ -203,6 +203,7 @@ class Context:
         self._dats = {}
         self._keep = []
         self._problems = 0  # FluxProblems declared on this context (their map names)
+        self._fixed_order = {}  # map -> whether its plan has the coloured iteration's lists
 
     @property
     def torch_device(self):
@@ -251,7 +252,10 @@ class Context:
         info = PlanInfo()
         self._check(self.lib.opf_plan(self._ctx, m, ctypes.byref(opts), ctypes.byref(info)),
                     "opf_plan")
-        return {k: getattr(info, k) for k, _ in PlanInfo._fields_}
+        out = {k: getattr(info, k) for k, _ in PlanInfo._fields_}
+        # whether the plan has lists for the coloured variant's fused iteration
+        self._fixed_order[m] = bool(out["coloured_ok"] and out["owner_ok"] and cluster_size <= 512)
+        return out
 
     def get_perm(self, s, size):
         out = np.empty(size, dtype=np.int32)
@@ -517,7 +521,7 @@ class FluxProblem:
             if like.ctx is not ctx:
                 raise ValueError("like= must be a problem on the same context")
             for k in ("N", "E", "nodes", "edges", "e2n", "info", "node_new", "edge_new", "tets",
-                      "t2n", "t2e", "cluster_size"):
+                      "t2n", "t2e"):
                 setattr(self, k, getattr(like, k))
         else:
             e2n = np.ascontiguousarray(e2n, dtype=np.int32)
@@ -542,7 +546,6 @@ class FluxProblem:
                                  cluster_size=cluster_size, lane_groups=lane_groups,
                                  owner_compact=owner_compact, bank_spread=bank_spread,
                                  halo_order=halo_order)
-            self.cluster_size = cluster_size
             self.node_new = ctx.get_perm(self.nodes, self.N)
             self.edge_new = ctx.get_perm(self.edges, self.E)
         dev = ctx.torch_device
@@ -595,10 +598,9 @@ class FluxProblem:
 
     def _fuses(self, variant):
         """Whether an iteration of this variant has its stage updates fused into its
-        edge loops: OWNER; COLOURED where the plan has fixed-order lists."""
+        edge loops: OWNER; COLOURED where the map's plan of now has fixed-order lists."""
         if variant == COLOURED:
-            return (self.info["coloured_ok"] and self.info["owner_ok"] and self.cluster_size <= 512
-                    and self._whole_ss())
+            return self.ctx._fixed_order.get(self.e2n, False) and self._whole_ss()
         return variant == OWNER
 
     def _whole_ss(self):
