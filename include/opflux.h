@@ -315,8 +315,10 @@ typedef struct {
  * contiguous edge ranges of at most block_size edges, grouped by colour;
  * (6) local indices resolve to the map's nodes; (7) colour counts fit their
  * types; (8) every edge is in the work of exactly the owner clusters of its
- * two endpoints, in the segments and in the visit lists alike; (9) every edge
- * has exactly one flat colour and edges of one flat colour share no node.
+ * two endpoints, in the segments and in the visit lists alike, and every end of
+ * every edge is once in the fixed-order loops' lists (built again to check them);
+ * (9) every edge has exactly one flat colour and edges of one flat colour share
+ * no node.
  * Works without a GPU.  Errors: OPF_EPLAN (report filled),
  * OPF_ESTATE (no plan), OPF_ENOMEM (not verified). */
 int opf_plan_verify(const opf_ctx *ctx, opf_map map, opf_plan_report *report);

@@ -1794,7 +1794,14 @@ int opf_plan_verify(const opf_ctx *ctx, opf_map map, opf_plan_report *report)
     if (it == ctx->plans.end()) return OPF_ESTATE;
     opf::VerifyResult vr;
     try {
-        vr = opf::verify_plan(it->second->host, ctx->maps[map].idx.data());
+        const opf::Plan &P = it->second->host;
+        vr = opf::verify_plan(P, ctx->maps[map].idx.data());
+        const int K = vr.ok && P.owner_ok ? fixed_chunk(P) : 0;
+        if (K) {
+            opf::FixedLists F;
+            opf::build_fixed(P, K, opf::gpu::kOwnerThreads, F);
+            vr = opf::verify_fixed(P, F, opf::gpu::kOwnerThreads);
+        }
     } catch (const std::bad_alloc &) {
         return OPF_ENOMEM;
     }

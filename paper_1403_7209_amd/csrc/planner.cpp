@@ -1016,6 +1016,86 @@ void build_fixed(const Plan &P, int K, int NT, FixedLists &F)
     });
 }
 
+VerifyResult verify_fixed(const Plan &P, const FixedLists &F, int NT)
+{
+    VerifyResult r;
+    auto fail = [&](int64_t where, const char *what) {
+        r.ok = false;
+        r.property = 8;
+        r.where = where;
+        r.message = std::string("fixed-order lists: ") + what;
+        return r;
+    };
+    const int64_t K = F.K, N = P.N, E = P.E;
+    if (K <= 0 || K > NT) return fail(-1, "chunk size");
+    const int64_t nch = (N + K - 1) / K;
+    if ((int64_t)F.cv_off.size() != nch + 1 || F.cv_off[0] != 0) return fail(-1, "visit offsets");
+    if (F.fine) {
+        const size_t nv = 2 * (size_t)E;
+        if ((int64_t)F.node_off.size() != N + 1 || F.node_off[0] != 0 || F.node_off[N] != 2 * E ||
+            F.cv_eid.size() != nv || F.cv_oth.size() != nv || F.cv_own.size() != nv)
+            return fail(-1, "sizes");
+        std::vector<uint8_t> interior(E, 0), seen(nv, 0);
+        for (int64_t c = 0; c < P.nclusters(); ++c)
+            std::fill_n(interior.begin() + P.cl_prim[2 * c], P.cl_nint[c], (uint8_t)1);
+        for (int64_t c = 0; c < nch; ++c)
+            if (F.cv_off[c + 1] != F.node_off[std::min(N, (c + 1) * K)]) return fail(c, "visit offsets");
+        for (int64_t v = 0; v < N; ++v) {
+            if (F.node_off[v + 1] < F.node_off[v]) return fail(v, "node offsets");
+            for (int64_t s = F.node_off[v]; s < F.node_off[v + 1]; ++s) {
+                const int64_t e = F.cv_eid[s], h = (uint32_t)F.cv_oth[s] >> 31;
+                if (e < 0 || e >= E || (F.cv_own[s] & 0x7fff) != v % K || P.e2n[2 * e + h] != v ||
+                    (F.cv_oth[s] & 0x7fffffff) != P.e2n[2 * e + 1 - h] || (F.cv_own[s] >> 15) != interior[e] ||
+                    seen[2 * e + h]++)
+                    return fail(v, "a visit is not one of the node's edge ends, or is there twice");
+            }
+        }
+        return r;
+    }
+    if (K != P.cluster_size || (int64_t)F.iblk.size() != 2 * nch || (int64_t)F.rnd_off.size() != nch + 1 ||
+        F.rnd_off[0] != 0)
+        return fail(-1, "sizes");
+    for (int64_t c = 0; c < nch; ++c) {
+        const int64_t n = (int64_t)P.cl_nint[c] + P.cl_cut_off[c + 1] - P.cl_cut_off[c];
+        if (F.iblk[2 * c] != P.cl_prim[2 * c] || F.iblk[2 * c + 1] != P.cl_nint[c] ||
+            F.cv_off[c + 1] != P.cl_cut_off[c + 1] || F.rnd_off[c + 1] - F.rnd_off[c] != (n + NT - 1) / NT)
+            return fail(c, "a chunk's visits or rounds");
+    }
+    const int64_t nr = F.rnd_off[nch];
+    if ((int64_t)F.ent_base.size() != nr + 1 || F.ent_base[0] != 0 || (int64_t)F.off.size() != nr * K ||
+        F.ent_base[nr] != (int64_t)F.ent.size())
+        return fail(-1, "sizes");
+    std::vector<uint8_t> seen(2 * (size_t)NT);
+    for (int64_t c = 0; c < nch; ++c) {
+        const int64_t i0 = F.iblk[2 * c], ni = F.iblk[2 * c + 1], s0 = F.cv_off[c];
+        const int64_t n = ni + F.cv_off[c + 1] - s0;
+        for (int64_t rr = F.rnd_off[c], b = 0; b < n; ++rr, b += NT) {
+            const int64_t e = std::min<int64_t>(n, b + NT), two = std::max<int64_t>(0, std::min(e, ni) - b);
+            const int64_t cnt = F.ent_base[rr + 1] - F.ent_base[rr];
+            if (cnt != e - b + two) return fail(c, "a round's entries");
+            std::fill(seen.begin(), seen.end(), 0);
+            int64_t at = 0;
+            for (int64_t k = 0; k < K; ++k) {
+                const uint32_t o = F.off[rr * K + k];
+                if ((int64_t)(o & 0xffffu) != at || (int64_t)(o >> 16) < at || (int64_t)(o >> 16) > cnt)
+                    return fail(c * K + k, "a node's entries in a round");
+                for (at = o & 0xffffu; at < (int64_t)(o >> 16); ++at) {
+                    const uint32_t en = F.ent[F.ent_base[rr] + at], slot = en & 0x7fffu, end = en >> 15;
+                    const int64_t kk = b + slot;
+                    if (kk >= e || (end && kk >= ni) || seen[2 * slot + end]++)
+                        return fail(c * K + k, "an entry is no visit of the round, or is there twice");
+                    const int64_t s = s0 + kk - ni;
+                    const int32_t v = kk < ni ? P.e2n[2 * (i0 + kk) + end]
+                                              : P.e2n[2 * (int64_t)P.cl_cute_eid[s] + P.cl_cute_end[s]];
+                    if (v != c * K + k) return fail(c * K + k, "an entry of another node");
+                }
+            }
+            if (at != cnt) return fail(c, "a round's entries");
+        }
+    }
+    return r;
+}
+
 VerifyResult verify_plan(const Plan &P, const int32_t *e2n_user)
 {
     VerifyResult r;

@@ -153,4 +153,9 @@ struct VerifyResult {
 // Bit-exact check of the plan's properties (1..9) against the user map.
 VerifyResult verify_plan(const Plan &plan, const int32_t *e2n_user);
 
+// Whether the lists hold every end of every edge exactly once, at its node, within
+// the bounds their kernels assume (NT: as given to build_fixed).  The plan itself
+// must have been verified.
+VerifyResult verify_fixed(const Plan &plan, const FixedLists &lists, int NT);
+
 }  // namespace opf
