@@ -8,9 +8,11 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <initializer_list>
 #include <map>
 #include <memory>
@@ -780,6 +782,14 @@ struct Rings {
     std::vector<uint16_t> ring, vloc;
 };
 
+// Runs f(c0, c1) over ranges of the chunks [0, n) on a few host threads: few enough
+// ranges that each can have an array over all nodes.
+void chunks_parallel(int64_t n, const std::function<void(int64_t, int64_t)> &f)
+{
+    const int64_t parts = std::min<int64_t>(n, 32);
+    opf::parallel_run(parts, [&](int64_t i) { f(i * n / parts, (i + 1) * n / parts); });
+}
+
 // Builds the ring form from the plan's internal edge->node map (e2n), the tets
 // in internal numbering (tn, 4 per tet) and the CSR list of the tets around
 // every edge (eo, el: tet * 8 + local edge, ascending tet order).  Chunks are
@@ -788,7 +798,8 @@ struct Rings {
 // the edge order, a chunk's nodes and halo exceed kGeoMaxRows, a batch of
 // kGeoThreads edges has more than kGeoMaxBatch entries, the edges at a chunk's
 // nodes exceed kGeoMaxSlots, or the tets around an edge are not one fan (each
-// next tet sharing a face with the last).
+// next tet sharing a face with the last).  Host threads share the chunks: this and
+// build_links are most of the first call on a mesh.
 bool build_rings(const std::vector<int32_t> &e2n, int64_t N, int64_t E, int KG,
                  const std::vector<int32_t> &tn, const std::vector<int32_t> &eo,
                  const std::vector<int32_t> &el, Rings &R)
@@ -807,30 +818,35 @@ bool build_rings(const std::vector<int32_t> &e2n, int64_t N, int64_t E, int KG,
         last[c] = e;
         ++R.chunk_e[2 * c + 1];
     }
+    std::atomic<bool> fits(true);
     // halo of every chunk: the other vertices of its edges' tets, ascending
     std::vector<std::vector<int32_t>> halo(nch);
-    std::vector<int32_t> mark(N, -1), loc(N, -1);
-    for (int64_t c = 0; c < nch; ++c) {
-        const int64_t v0 = c * KG, v1 = std::min<int64_t>(N, v0 + KG);
-        std::vector<int32_t> &h = halo[c];
-        auto see = [&](int32_t v) {
-            if ((v < v0 || v >= v1) && mark[v] != (int32_t)c) {
-                mark[v] = (int32_t)c;
-                h.push_back(v);
+    chunks_parallel(nch, [&](int64_t c0, int64_t c1) {
+        std::vector<int32_t> mark(N, -1);
+        for (int64_t c = c0; c < c1; ++c) {
+            const int64_t v0 = c * KG, v1 = std::min<int64_t>(N, v0 + KG);
+            std::vector<int32_t> &h = halo[c];
+            auto see = [&](int32_t v) {
+                if ((v < v0 || v >= v1) && mark[v] != (int32_t)c) {
+                    mark[v] = (int32_t)c;
+                    h.push_back(v);
+                }
+            };
+            for (int64_t e = R.chunk_e[2 * c]; e < R.chunk_e[2 * c] + R.chunk_e[2 * c + 1]; ++e) {
+                see(e2n[2 * e]);
+                see(e2n[2 * e + 1]);
+                for (int32_t j = eo[e]; j < eo[e + 1]; ++j) {
+                    const int32_t t = el[j] >> 3;
+                    for (int v = 0; v < 4; ++v) see(tn[4 * (int64_t)t + v]);
+                }
             }
-        };
-        for (int64_t e = R.chunk_e[2 * c]; e < R.chunk_e[2 * c] + R.chunk_e[2 * c + 1]; ++e) {
-            see(e2n[2 * e]);
-            see(e2n[2 * e + 1]);
-            for (int32_t j = eo[e]; j < eo[e + 1]; ++j) {
-                const int32_t t = el[j] >> 3;
-                for (int v = 0; v < 4; ++v) see(tn[4 * (int64_t)t + v]);
-            }
+            std::sort(h.begin(), h.end());
+            if (KG + (int64_t)h.size() > opf::gpu::kGeoMaxRows) fits = false;
+            if (!fits) return;
         }
-        std::sort(h.begin(), h.end());
-        if (KG + (int64_t)h.size() > opf::gpu::kGeoMaxRows) return false;
-        R.L = std::max<int>(R.L, KG + (int)h.size());
-    }
+    });
+    if (!fits) return false;
+    for (int64_t c = 0; c < nch; ++c) R.L = std::max<int>(R.L, KG + (int)halo[c].size());
     R.halo_off.assign(nch + 1, 0);
     for (int64_t c = 0; c < nch; ++c) R.halo_off[c + 1] = R.halo_off[c] + (int32_t)halo[c].size();
     R.halo.resize(R.halo_off[nch]);
@@ -851,9 +867,9 @@ bool build_rings(const std::vector<int32_t> &e2n, int64_t N, int64_t E, int KG,
             R.RB = std::max<int>(R.RB, (int)n);
         }
     }
-    std::vector<int32_t> pr, ps;
-    std::vector<uint8_t> used;
-    for (int64_t c = 0; c < nch; ++c) {
+    // chunk c's chains; false: its tets are not one fan around some edge
+    auto chains = [&](int64_t c, std::vector<int32_t> &loc, std::vector<int32_t> &pr,
+                      std::vector<int32_t> &ps, std::vector<uint8_t> &used) {
         const int64_t v0 = c * KG;
         const std::vector<int32_t> &h = halo[c];
         for (size_t i = 0; i < h.size(); ++i) loc[h[i]] = KG + (int32_t)i;
@@ -906,7 +922,17 @@ bool build_rings(const std::vector<int32_t> &e2n, int64_t N, int64_t E, int KG,
                 R.ring[o++] = local(last);
             }
         }
-    }
+        return true;
+    };
+    chunks_parallel(nch, [&](int64_t c0, int64_t c1) {
+        std::vector<int32_t> loc(N, -1), pr, ps;
+        std::vector<uint8_t> used;
+        for (int64_t c = c0; c < c1; ++c) {
+            if (!chains(c, loc, pr, ps, used)) fits = false;
+            if (!fits) return;
+        }
+    });
+    if (!fits) return false;
     // incident edges of every node, ascending edge order
     std::vector<int32_t> n2e_off(N + 1, 0), n2e(2 * E);
     for (int64_t e = 0; e < E; ++e) {
@@ -926,18 +952,20 @@ bool build_rings(const std::vector<int32_t> &e2n, int64_t N, int64_t E, int KG,
     R.vsec_off.assign(nch + 1, 0);
     R.vloc_off = n2e_off;
     R.vloc.resize(2 * E);
-    std::vector<int32_t> sec;
-    for (int64_t c = 0; c < nch; ++c) {
+    std::vector<std::vector<int32_t>> secs(nch);
+    opf::parallel_run(nch, [&](int64_t c) {
         const int64_t v0 = c * KG, v1 = std::min<int64_t>(N, v0 + KG);
         const int64_t first = R.chunk_e[2 * c], count = R.chunk_e[2 * c + 1];
-        sec.clear();
+        std::vector<int32_t> &sec = secs[c];
         for (int64_t i = v0; i < v1; ++i)
             for (int32_t j = n2e_off[i]; j < n2e_off[i + 1]; ++j)
                 if (n2e[j] < first || n2e[j] >= first + count) sec.push_back(n2e[j]);
         std::sort(sec.begin(), sec.end());
         sec.erase(std::unique(sec.begin(), sec.end()), sec.end());
-        if (count + (int64_t)sec.size() > opf::gpu::kGeoMaxSlots) return false;
-        R.DV = std::max<int>(R.DV, (int)(count + sec.size()));
+        if (count + (int64_t)sec.size() > opf::gpu::kGeoMaxSlots) {
+            fits = false;
+            return;
+        }
         for (int64_t i = v0; i < v1; ++i)
             for (int32_t j = n2e_off[i]; j < n2e_off[i + 1]; ++j) {
                 const int64_t e = n2e[j];
@@ -945,8 +973,12 @@ bool build_rings(const std::vector<int32_t> &e2n, int64_t N, int64_t E, int KG,
                                            ? e - first
                                            : count + (std::lower_bound(sec.begin(), sec.end(), (int32_t)e) - sec.begin()));
             }
-        R.vsec_off[c + 1] = R.vsec_off[c] + (int32_t)sec.size();
-        R.vsec.insert(R.vsec.end(), sec.begin(), sec.end());
+    });
+    if (!fits) return false;
+    for (int64_t c = 0; c < nch; ++c) {
+        R.vsec_off[c + 1] = R.vsec_off[c] + (int32_t)secs[c].size();
+        R.vsec.insert(R.vsec.end(), secs[c].begin(), secs[c].end());
+        R.DV = std::max<int>(R.DV, (int)(R.chunk_e[2 * c + 1] + secs[c].size()));
     }
     return true;
 }
@@ -956,6 +988,40 @@ struct Links {
     int nchunk = 0, lds = 0;
     std::vector<int32_t> node, edge_off, edge, halo_off, halo, ent_off;
     std::vector<uint32_t> ends, ent;
+};
+
+// Numbers the distinct values it is given 0, 1, ... (a hash table, open addressing).
+struct Numbering {
+    std::vector<int32_t> values;  // by number
+    explicit Numbering(size_t expected)
+    {
+        size_t n = 64;
+        while (n < 2 * expected) n *= 2;
+        table.assign(n, -1);
+        values.reserve(expected);
+    }
+    int32_t of(int32_t v)
+    {
+        if (2 * values.size() >= table.size()) {
+            table.assign(2 * table.size(), -1);
+            for (size_t i = 0; i < values.size(); ++i) table[place(values[i])] = (int32_t)i;
+        }
+        int32_t &t = table[place(v)];
+        if (t < 0) {
+            t = (int32_t)values.size();
+            values.push_back(v);
+        }
+        return t;
+    }
+
+  private:
+    std::vector<int32_t> table;
+    size_t place(int32_t v) const
+    {
+        size_t k = ((uint32_t)v * 2654435769u >> 7) & (table.size() - 1);
+        while (table[k] >= 0 && values[table[k]] != v) k = (k + 1) & (table.size() - 1);
+        return k;
+    }
 };
 
 // Builds the link form from the chains of the ring form.  Returns false, and the
@@ -978,25 +1044,35 @@ bool build_links(const std::vector<int32_t> &e2n, int64_t N, int64_t E, const Ri
             c.push_back(l < R.KG ? (int32_t)(k * R.KG + l) : R.halo[R.halo_off[k] + l - R.KG]);
         }
     };
-    std::vector<int64_t> off(N + 1, 0);
-    std::vector<int32_t> c;
-    for (int64_t e = 0; e < E; ++e) {
-        chain(e, c);
-        if (c.size() == 1) continue;  // no tets
-        if (c.size() < 4 || c.front() != c.back()) return false;
-        for (size_t i = 1; i < c.size(); ++i) ++off[c[i] + 1];
+    for (int64_t e = 0; e < E; ++e) {  // an open fan ends this before anything is built
+        const int32_t j0 = R.ring_off[e] + 2, j1 = R.ring_off[e + 1];
+        if (j1 - j0 != 1 && (j1 - j0 < 4 || R.ring[j0] != R.ring[j1 - 1])) return false;
     }
+    constexpr int64_t kEdges = 16384;  // of one task
+    const int64_t ne = (E + kEdges - 1) / kEdges;
+    std::vector<int64_t> off(N + 1, 0);
+    opf::parallel_run(ne, [&](int64_t b) {
+        std::vector<int32_t> c;
+        for (int64_t e = b * kEdges; e < std::min<int64_t>(E, (b + 1) * kEdges); ++e) {
+            chain(e, c);
+            for (size_t i = 1; i < c.size(); ++i) __atomic_fetch_add(&off[c[i] + 1], 1, __ATOMIC_RELAXED);
+        }
+    });
     for (int64_t i = 0; i < N; ++i) off[i + 1] += off[i];
     if (off[N] >= ((int64_t)1 << 31)) return false;
     std::vector<Item> item(off[N]);
     {
         std::vector<int64_t> fill(off.begin(), off.end() - 1);
-        for (int64_t e = 0; e < E; ++e) {
-            chain(e, c);
-            const size_t k = c.size() - 1;
-            for (size_t i = 0; i < k; ++i)
-                item[fill[c[i]]++] = Item{(int32_t)e, c[i == 0 ? k - 1 : i - 1], c[i + 1]};
-        }
+        opf::parallel_run(ne, [&](int64_t b) {
+            std::vector<int32_t> c;
+            for (int64_t e = b * kEdges; e < std::min<int64_t>(E, (b + 1) * kEdges); ++e) {
+                chain(e, c);
+                const size_t k = c.size() - 1;
+                for (size_t i = 0; i < k; ++i)
+                    item[__atomic_fetch_add(&fill[c[i]], 1, __ATOMIC_RELAXED)] =
+                        Item{(int32_t)e, c[i == 0 ? k - 1 : i - 1], c[i + 1]};
+            }
+        });
     }
     // chunks: consecutive nodes until the next one would exceed the LDS, within
     // blocks of nodes that are independent of one another
@@ -1009,26 +1085,25 @@ bool build_links(const std::vector<int32_t> &e2n, int64_t N, int64_t E, const Ri
     opf::parallel_run(nb, [&](int64_t b) {
         Links &P = part[b];
         const int64_t b0 = b * kBlock, b1 = std::min<int64_t>(N, b0 + kBlock);
-        // the block's edges and neighbours, and the chunk that last took each
-        std::vector<int32_t> es, us;
+        for (int64_t v = b0; v < b1; ++v)  // in edge order whichever thread came first
+            std::sort(item.begin() + off[v], item.begin() + off[v + 1], [](const Item &x, const Item &y) {
+                return x.e != y.e ? x.e < y.e : x.r != y.r ? x.r < y.r : x.s < y.s;
+            });
+        // the block's edges and neighbours, numbered (in place of their labels in the
+        // items), and the chunk that last took each
+        Numbering enums(16 * kBlock), unums(4 * kBlock);
+        for (int64_t v = b0; v < b1; ++v) unums.of((int32_t)v);
         for (int64_t j = off[b0]; j < off[b1]; ++j) {
-            es.push_back(item[j].e);
-            us.push_back(item[j].r);
-            us.push_back(item[j].s);
+            Item &x = item[j];
+            x = Item{enums.of(x.e), unums.of(x.r), unums.of(x.s)};
         }
-        for (int64_t v = b0; v < b1; ++v) us.push_back((int32_t)v);
-        for (std::vector<int32_t> *x : {&es, &us}) {
-            std::sort(x->begin(), x->end());
-            x->erase(std::unique(x->begin(), x->end()), x->end());
-        }
-        auto at = [](const std::vector<int32_t> &x, int32_t v) {
-            return (size_t)(std::lower_bound(x.begin(), x.end(), v) - x.begin());
-        };
+        const std::vector<int32_t> &es = enums.values, &us = unums.values;
+        const int32_t nus = (int32_t)us.size();
         std::vector<int32_t> etaken(es.size(), -1), utaken(us.size(), -1), eslot(es.size()), urow(us.size());
         std::vector<int32_t> ce, cu, ne, nu;
         auto close = [&](int64_t v0, int64_t v1) {
-            std::sort(ce.begin(), ce.end());
-            std::sort(cu.begin(), cu.end());
+            std::sort(ce.begin(), ce.end(), [&](int32_t x, int32_t y) { return es[x] < es[y]; });
+            std::sort(cu.begin(), cu.end(), [&](int32_t x, int32_t y) { return us[x] < us[y]; });
             P.node.push_back((int32_t)v0);
             int rows = (int)(v1 - v0);
             for (int32_t u : cu) {
@@ -1044,19 +1119,20 @@ bool build_links(const std::vector<int32_t> &e2n, int64_t N, int64_t E, const Ri
                 eslot[ce[i]] = (int32_t)i;
                 const int64_t e = es[ce[i]];
                 P.edge.push_back((int32_t)e);
-                P.ends.push_back((uint32_t)urow[at(us, e2n[2 * e])] |
-                                 ((uint32_t)urow[at(us, e2n[2 * e + 1])] << 16));
+                const int32_t p = unums.of(e2n[2 * e]), q = unums.of(e2n[2 * e + 1]);
+                if (p >= nus || q >= nus) return false;  // an end that is no neighbour
+                P.ends.push_back((uint32_t)urow[p] | ((uint32_t)urow[q] << 16));
             }
             P.edge_off.push_back((int32_t)P.edge.size());
             P.halo_off.push_back((int32_t)P.halo.size());
             P.lds = std::max(P.lds, link_lds(rows, (int)ce.size()));
             for (int64_t j = off[v0]; j < off[v1]; ++j)
-                K.ent[j] = (uint32_t)eslot[at(es, item[j].e)] |
-                           ((uint32_t)urow[at(us, item[j].r)] << 12) |
-                           ((uint32_t)urow[at(us, item[j].s)] << 22);
+                K.ent[j] = (uint32_t)eslot[item[j].e] | ((uint32_t)urow[item[j].r] << 12) |
+                           ((uint32_t)urow[item[j].s] << 22);
             ++P.nchunk;
             ce.clear();
             cu.clear();
+            return true;
         };
         int64_t v0 = b0;
         for (int64_t v = b0; v < b1; ++v) {
@@ -1065,18 +1141,16 @@ bool build_links(const std::vector<int32_t> &e2n, int64_t N, int64_t E, const Ri
                 // its neighbours too: each is the r or s of another of its entries)
                 ne.clear();
                 nu.clear();
-                auto take = [&](const std::vector<int32_t> &x, std::vector<int32_t> &taken, int32_t id,
-                                std::vector<int32_t> &news) {
-                    const size_t i = at(x, id);
+                auto take = [&](std::vector<int32_t> &taken, int32_t i, std::vector<int32_t> &news) {
                     if (taken[i] == P.nchunk) return;
                     taken[i] = P.nchunk;
-                    news.push_back((int32_t)i);
+                    news.push_back(i);
                 };
-                take(us, utaken, (int32_t)v, nu);
+                take(utaken, (int32_t)(v - b0), nu);
                 for (int64_t j = off[v]; j < off[v + 1]; ++j) {
-                    take(es, etaken, item[j].e, ne);
-                    take(us, utaken, item[j].r, nu);
-                    take(us, utaken, item[j].s, nu);
+                    take(etaken, item[j].e, ne);
+                    take(utaken, item[j].r, nu);
+                    take(utaken, item[j].s, nu);
                 }
                 const int64_t ns = (int64_t)(ce.size() + ne.size()), nr = (int64_t)(cu.size() + nu.size());
                 if (v - v0 < kLinkNodes && ns <= kLinkSlots && nr <= kLinkRows &&
@@ -1091,11 +1165,14 @@ bool build_links(const std::vector<int32_t> &e2n, int64_t N, int64_t E, const Ri
                 }
                 for (int32_t i : ne) etaken[i] = -1;
                 for (int32_t i : nu) utaken[i] = -1;
-                close(v0, v);
+                if (!close(v0, v)) {
+                    bad[b] = 1;
+                    return;
+                }
                 v0 = v;
             }
         }
-        close(v0, b1);
+        if (!close(v0, b1)) bad[b] = 1;
     });
     K.edge_off.assign(1, 0);
     K.halo_off.assign(1, 0);
