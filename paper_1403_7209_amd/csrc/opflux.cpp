@@ -201,7 +201,7 @@ int upload_owner(opf_ctx *ctx, PlanRec &pr)
     const int64_t ncl = P.nclusters();
     std::vector<int2> iblk(ncl);
     std::vector<uint32_t> iw(P.E, 0);
-    for (int64_t c = 0; c < ncl; ++c) {
+    opf::parallel_run(ncl, [&](int64_t c) {
         const int32_t p0 = P.cl_prim[2 * c], ni = P.cl_nint[c];
         iblk[c] = make_int2(p0, ni);
         for (int64_t e = p0; e < p0 + ni; ++e) {
@@ -209,7 +209,7 @@ int upload_owner(opf_ctx *ctx, PlanRec &pr)
             iw[e] = (uint32_t)(P.e2n[2 * e] - c * K) | ((uint32_t)(P.e2n[2 * e + 1] - c * K) << 16) |
                     (sw << 31);
         }
-    }
+    }, P.E);
     const size_t nv = P.cl_cut_eid.size();
     std::vector<int> cv_off(ncl + 1);
     for (int64_t c = 0; c <= ncl; ++c) cv_off[c] = (int)P.cl_cut_off[c];
@@ -222,13 +222,14 @@ int upload_owner(opf_ctx *ctx, PlanRec &pr)
         const std::vector<uint8_t> &ch = order == 2 ? P.cl_cute_end : order ? P.cl_cutf_end : P.cl_cut_end;
         std::vector<int> cv_oth(nv);
         std::vector<uint16_t> cv_own(nv);
-        for (int64_t c = 0; c < ncl; ++c)
+        opf::parallel_run(ncl, [&](int64_t c) {
             for (int64_t s = P.cl_cut_off[c]; s < P.cl_cut_off[c + 1]; ++s) {
                 const int64_t e = ce[s];
                 const int h = ch[s];
                 cv_oth[s] = (int)((uint32_t)P.e2n[2 * e + 1 - h] | ((uint32_t)h << 31));
                 cv_own[s] = (uint16_t)(P.e2n[2 * e + h] - c * K);
             }
+        }, (int64_t)nv);
         rc = upload(ctx, pr, ce, order == 2 ? D.cve_eid : order ? D.cvf_eid : D.cv_eid);
         if (!rc) rc = upload(ctx, pr, cv_oth, order == 2 ? D.cve_oth : order ? D.cvf_oth : D.cv_oth);
         if (!rc) rc = upload(ctx, pr, cv_own, order == 2 ? D.cve_own : order ? D.cvf_own : D.cv_own);

@@ -163,11 +163,14 @@ void morton(int64_t N, const double *xyz, std::vector<int32_t> &new_of_old)
 
 inline int lowest_free(uint64_t used) { return used == ~0ULL ? -1 : __builtin_ctzll(~used); }
 
-// Runs f(0..n-1) on up to 16 host threads (independent iterations only).
+// Runs f(0..n-1) on up to 16 host threads (independent iterations only).  items: of
+// what the loop handles, where that is little per item: a thread takes about as
+// long to start as to copy 65,536 of them.
 template <class F>
-void parallel_for(int64_t n, const F &f)
+void parallel_for(int64_t n, const F &f, int64_t items = INT64_MAX)
 {
-    const int64_t nt = std::max<int64_t>(1, std::min<int64_t>({16, (int64_t)std::thread::hardware_concurrency(), n}));
+    const int64_t nt = std::max<int64_t>(
+        1, std::min<int64_t>({16, (int64_t)std::thread::hardware_concurrency(), n, items / 65536}));
     if (nt <= 1) {
         for (int64_t i = 0; i < n; ++i) f(i);
         return;
@@ -800,14 +803,14 @@ int build_plan(int64_t N, int64_t E, const int32_t *e2n_user, const PlanOptions 
         P.cl_cutf_end.resize(P.cl_cut_off[ncl]);
         P.cl_cute_eid.resize(P.cl_cut_off[ncl]);
         P.cl_cute_end.resize(P.cl_cut_off[ncl]);
-        for (int64_t c = 0; c < ncl; ++c) {
+        parallel_for(ncl, [&](int64_t c) {
             std::copy(cut_eid[c].begin(), cut_eid[c].end(), P.cl_cut_eid.begin() + P.cl_cut_off[c]);
             std::copy(cut_end[c].begin(), cut_end[c].end(), P.cl_cut_end.begin() + P.cl_cut_off[c]);
             std::copy(cutf_eid[c].begin(), cutf_eid[c].end(), P.cl_cutf_eid.begin() + P.cl_cut_off[c]);
             std::copy(cutf_end[c].begin(), cutf_end[c].end(), P.cl_cutf_end.begin() + P.cl_cut_off[c]);
             std::copy(cute_eid[c].begin(), cute_eid[c].end(), P.cl_cute_eid.begin() + P.cl_cut_off[c]);
             std::copy(cute_end[c].begin(), cute_end[c].end(), P.cl_cute_end.begin() + P.cl_cut_off[c]);
-        }
+        }, P.cl_cut_off[ncl]);
         P.owner_ok = true;
     }
 
@@ -930,7 +933,7 @@ int build_plan(int64_t N, int64_t E, const int32_t *e2n_user, const PlanOptions 
     return OPF_OK;
 }
 
-void parallel_run(int64_t n, const std::function<void(int64_t)> &f) { parallel_for(n, f); }
+void parallel_run(int64_t n, const std::function<void(int64_t)> &f, int64_t items) { parallel_for(n, f, items); }
 
 void build_fixed(const Plan &P, int K, int NT, FixedLists &F)
 {
@@ -955,6 +958,8 @@ void build_fixed(const Plan &P, int K, int NT, FixedLists &F)
         F.cv_eid.resize(2 * P.E);
         F.cv_oth.resize(2 * P.E);
         F.cv_own.resize(2 * P.E);
+        std::vector<uint16_t> place(P.N);  // of each node in its chunk
+        for (int64_t v = 0, k = 0; v < P.N; ++v, k = k + 1 == K ? 0 : k + 1) place[v] = (uint16_t)k;
         std::vector<uint16_t> interior(P.E, 0);
         for (int64_t c = 0; c < P.nclusters(); ++c)
             std::fill_n(interior.begin() + P.cl_prim[2 * c], P.cl_nint[c], (uint16_t)0x8000);
@@ -964,7 +969,7 @@ void build_fixed(const Plan &P, int K, int NT, FixedLists &F)
                 const int64_t s = at[v]++;
                 F.cv_eid[s] = (int32_t)e;
                 F.cv_oth[s] = (int32_t)((uint32_t)P.e2n[2 * e + 1 - h] | ((uint32_t)h << 31));
-                F.cv_own[s] = (uint16_t)((v % K) | interior[e]);
+                F.cv_own[s] = (uint16_t)(place[v] | interior[e]);
             }
         // at[v] is now past node v's last visit
         F.node_off.assign(P.N + 1, 0);
@@ -1263,9 +1268,17 @@ VerifyResult verify_plan(const Plan &P, const int32_t *e2n_user)
             P.cl_cutf_end.size() != P.cl_cut_eid.size() || P.cl_cute_eid.size() != P.cl_cut_eid.size() ||
             P.cl_cute_end.size() != P.cl_cut_eid.size())
             return fail(8, -1, "interior blocks or cut visits are inconsistent");
-        for (int order = 0; order < 3; ++order) {
+        VerifyResult of_order[3];
+        parallel_for(3, [&](int64_t order) {
             const std::vector<int32_t> &ce = order == 2 ? P.cl_cute_eid : order ? P.cl_cutf_eid : P.cl_cut_eid;
             const std::vector<uint8_t> &ch = order == 2 ? P.cl_cute_end : order ? P.cl_cutf_end : P.cl_cut_end;
+            auto fail = [&](int property, int64_t where, const char *msg) {
+                VerifyResult &o = of_order[order];
+                o.ok = false;
+                o.property = property;
+                o.where = where;
+                o.message = msg;
+            };
             std::vector<uint8_t> ends(E, 0);  // bit h: end h covered
             for (int64_t c = 0; c < ncl; ++c) {
                 const int64_t p0 = P.cl_prim[2 * c], ni = P.cl_nint[c];
@@ -1287,7 +1300,9 @@ VerifyResult verify_plan(const Plan &P, const int32_t *e2n_user)
             }
             for (int64_t k = 0; k < E; ++k)
                 if (ends[k] != 3) return fail(8, k, "edge end missing from the owner kernel's loops");
-        }
+        }, 2 * E);
+        for (const VerifyResult &o : of_order)
+            if (!o.ok) return o;
     }
     // (9) flat colouring: every edge in exactly one colour; edges of one colour
     // share no node

@@ -140,8 +140,8 @@ struct FixedLists {
 // K < cluster_size, over chunks of K nodes with visits of their own.
 void build_fixed(const Plan &plan, int K, int NT, FixedLists &out);
 
-// Runs f(0) .. f(n - 1) on a few host threads.
-void parallel_run(int64_t n, const std::function<void(int64_t)> &f);
+// Runs f(0) .. f(n - 1) on a few host threads; on fewer, or none, for few items.
+void parallel_run(int64_t n, const std::function<void(int64_t)> &f, int64_t items = INT64_MAX);
 
 struct VerifyResult {
     bool ok = true;
