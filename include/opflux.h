@@ -102,10 +102,12 @@ typedef enum {
 typedef enum {
     OPF_V_COLOURED = 0, /* the plan of Sec. 4.1; deterministic.  Where the plan
                            has owner clusters of at most 512 nodes, a single
-                           launch over them whose sums run in a fixed order;
-                           else mini-partitions staged in LDS, edge colours
-                           serialised inside a partition, one launch per
-                           partition colour                                       */
+                           launch over them (over smaller chunks up to 98,304
+                           nodes) whose sums run in a fixed order: block_size and
+                           colour_sort then only decide whether the plan has the
+                           two-level colouring this variant asks for.  Else
+                           mini-partitions staged in LDS, edge colours serialised
+                           inside a partition, one launch per partition colour    */
     OPF_V_ATOMIC = 1,   /* one thread per edge, FP64 atomic adds to HBM          */
     OPF_V_OWNER = 2,    /* one workgroup per cluster of consecutive nodes runs
                            every edge touching the cluster (edges between two

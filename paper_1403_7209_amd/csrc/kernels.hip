@@ -900,10 +900,10 @@ __device__ __forceinline__ void lds_sum6(const double (&acc)[6], double *buf, do
 //   (2) the cut visits: one (edge, owned end) pair each; the owned end's
 //       record comes from LDS, the other end's state is gathered from memory
 //       and staged in registers.  The flux is evaluated with the owned end as
-//       the first node: F(a, b, w) = -F(b, a, -w) for every kernel here (the
-//       edge inputs flip sign with the orientation), so a visit whose owned
-//       end is the edge's second node negates its edge inputs and adds the
-//       first-node result.  An edge joining two clusters runs in both.
+//       the first node: F(a, b, w) = -F(b, a, -w) for every kernel here, but for
+//       rounding (the edge inputs flip sign with the orientation), so a visit
+//       whose owned end is the edge's second node negates its edge inputs and adds
+//       the first-node result.  An edge joining two clusters runs in both.
 // KC > 0 fixes the cluster size at compile time (LDS addresses become
 // immediate offsets); KC = 0 takes it from the launch.
 __host__ __device__ constexpr int owner_acc_rows(int K) { return K; }
@@ -1199,7 +1199,7 @@ struct FixedTune {
     static constexpr int WAVES = 6, AHEAD = 4;
 };
 template <>
-struct FixedTune<double, OpAdjoint> {
+struct FixedTune<double, OpAdjoint> {  // two workgroups per CU, for three spilled registers
     static constexpr int WAVES = 4, AHEAD = 1;
 };
 template <>
@@ -1240,10 +1240,10 @@ __device__ __forceinline__ double stage_one(const StagePtrs<T> &sp, int v, int g
 // It serves the coloured variant: against one launch per partition colour, each
 // re-reading and re-writing the nodes' totals with a barrier per edge colour,
 // one launch that writes each total once (FP64 flux of a 1M-node mesh in RCM
-// order: 740 -> 190 us).  What bounds it there is latency: 64 % of the edges are
+// order: 727 -> 182 us).  What bounds it there is latency: 64 % of the edges are
 // cut, a chunk takes 11 rounds of two dependent trips to memory and two
 // barriers, and its wavefronts wait 80 % of their time (LDS pipe 30 % busy).
-// The owner kernel's atomics need no rounds and take 110 us on that mesh, but
+// The owner kernel's atomics need no rounds and take 105 us on that mesh, but
 // their order varies.
 // An FP32 cut edge is evaluated its first node first in both its clusters (the two
 // records are exchanged where the owned end is the second), so that its two
@@ -1374,9 +1374,9 @@ __global__ __launch_bounds__(kOwnerThreads, (FixedTune<T, Op>::WAVES)) void k_ed
 // node, go one per thread, all loads of a step in flight together and no record
 // staged (both ends' states are gathered); a node's slots are then one range,
 // which the NT / K threads of the node add up, NV of its NOUT sums each.  Three
-// trips to memory (offsets, visits, records) and one barrier: 5.8 us per FP64
-// stage at 8,000 nodes, 250 workgroups on 256 CUs, where staged records and entry
-// lists took 6.6 and sixteen 512-node clusters 13.5.
+// trips to memory (offsets, visits, records) and one barrier: the FP64 flux at
+// 8,000 nodes, 250 workgroups on 256 CUs, takes 4.5 us in a graph of launches, over
+// sixteen 512-node clusters 9.5; staged records and entry lists took 0.8 us more.
 // An FP32 edge is evaluated its first node first for both ends (one_way).  turn: an
 // edge between two owner clusters from its owned end, as the owner loop over the
 // clusters does, so that a mesh's FP32 results don't depend on which of the two

@@ -241,8 +241,8 @@ int upload_owner(opf_ctx *ctx, PlanRec &pr)
 // 98,304 nodes.  There 512-node chunks number at most 192, a workgroup each on
 // 256 CUs, and a chunk's 11 rounds follow one another; 32-node chunks run every
 // edge from both ends but take one round each.  Five fused stages of the FP64
-// flux in RCM order with 512- and 32-node chunks: 91,125 nodes 171 and 160 us,
-// 117,649 nodes 175 and 195 us.
+// flux in RCM order with 512- and 32-node chunks: 91,125 nodes 173 and 156 us,
+// 117,649 nodes 176 and 191 us.
 int fixed_chunk(const opf::Plan &P)
 {
     const int K = P.cluster_size;
@@ -536,13 +536,12 @@ int check_gbl_disjoint(opf_ctx *ctx, const void *p, size_t bytes, std::initializ
 // Whether a loop of this variant runs over the plan's fixed-order lists: the
 // coloured variant wherever there are any (the same fixed order on every run,
 // without a launch per partition colour); the owner variant up to 48 clusters,
-// which take as long as one of them does: flux and adjoint with 512-node clusters
-// at 8,000 nodes 5.5 and 7.5 us against 11.2 and 14.4 over the clusters, at 21,952
-// 8.8 and 12.7 against 11.7 and 15.4, at 46,656 14.2 and 21.9 against 12.2 and
-// 16.4.  Smaller clusters take less time each: adjoint and second-order flux at
-// 21,952 nodes 10.7 and 17.3 us against 7.8 and 12.1 over 64-node clusters, 11.5
-// and 17.5 against 11.4 and 14.2 over 256-node ones; at 12,167 nodes 8.2 and 11.5
-// against 6.7 and 9.3 over 64-node ones.
+// which take as long as one of them does.  Flux and adjoint in a graph of launches,
+// us, against the loop over 512-node clusters: 8,000 nodes 4.5 and 5.8 (9.5 and
+// 13.6), 21,952 8.6 and 11.2 (9.8 and 14.1), 46,656 12.7 and 21.0 (10.2 and 15.9).
+// Smaller clusters take less time each: over 256-node ones 12,167 nodes 5.6 and 8.1
+// (7.5 and 10.6), 21,952 8.4 and 11.2 (7.6 and 11.0); over 64-node ones 8,000 nodes
+// 4.2 and 5.5 (4.5 and 5.7), 12,167 5.4 and 7.6 (4.5 and 6.0).
 bool takes_fixed(const PlanRec &pr, int variant)
 {
     const opf::gpu::FixedPlan &X = pr.dev.fixed;
