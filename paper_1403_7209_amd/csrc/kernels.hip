@@ -1240,7 +1240,7 @@ __device__ __forceinline__ double stage_one(const StagePtrs<T> &sp, int v, int g
 // It serves the coloured variant: against one launch per partition colour, each
 // re-reading and re-writing the nodes' totals with a barrier per edge colour,
 // one launch that writes each total once (FP64 flux of a 1M-node mesh in RCM
-// order: 727 -> 182 us).  What bounds it there is latency: 64 % of the edges are
+// order: 727 -> 182 us).  What bounds it there is latency: 62 % of the edges are
 // cut, a chunk takes 11 rounds of two dependent trips to memory and two
 // barriers, and its wavefronts wait 80 % of their time (LDS pipe 30 % busy).
 // The owner kernel's atomics need no rounds and take 105 us on that mesh, but
